@@ -169,6 +169,7 @@ stencil_status build_generic_tables(stencil_plan_s *p, const stencil_desc *d) {
     sp->R = r;
     sp->eb = elem_bytes(d->dtype);
     sp->corners = t.corners;
+    sp->row_bytes = p->g.py * (long long)sp->eb;
     sp->slots.resize(ns);
     for (int s = 0; s < ns; ++s)
         for (int gi = slot_g[s]; gi < slot_g[s + 1]; ++gi) {
@@ -401,6 +402,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
     int v = dv;
     if (v == STENCIL_AUTO) v = has_sat ? V_SATURATED : V_PLAIN;
     Tile t = default_tile(p->kind, is_point_form(v) ? V_PLAIN : v, p->g);
+    if (p->kind == STENCIL_GENERIC && v == V_SATURATED && !d->tile_x && !d->tile_y) t = rtc_default_tile(*p->rtc, p->g);
     if (d->tile_x) t.tx = d->tile_x;
     if (d->tile_y) t.ty = d->tile_y;
     if (d->zblock) t.tz = d->zblock;

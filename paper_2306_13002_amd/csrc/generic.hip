@@ -10,15 +10,17 @@
 // table (linear offset, coefficient per tap) is uniform across the launch,
 // so it is read through the scalar cache.
 //
-// SATURATED: the paper's rewrites on the tap sum.  COMM/ASSOC gather the
-// taps that share a coefficient id AND a z offset into one group, summed
-// first (taps in ascending address order) and multiplied once with an FMA
-// (FMA1).  Loads: a block owns a TX x TY column tile and streams input
-// planes; each plane is staged once in LDS (with its r-wide ring, corners
-// included) and contributes to the 2r+1 output planes it touches, which
-// wait in a register queue of FP64 accumulators (plane accumulation), so
-// every input value is read from memory once per block.  The next plane's
-// loads are issued before the current plane's arithmetic.
+// SATURATED: the paper's rewrites on the tap sum.  Loads: a block owns a
+// column tile and streams input planes; each plane is staged once in LDS (with
+// its r-wide ring, corners included where a tap needs them) and contributes
+// to the 2r+1 output planes it touches, which wait in a register queue of FP64
+// accumulators (plane accumulation), so every input value is read from memory
+// once per block.  The next plane's loads are issued before the current
+// plane's arithmetic.  The kernels generated for one stencil (rtc.cpp) choose
+// between sums shared among the slots and one FMA per tap.  The table-driven
+// kernel here (the fallback, and the allocation-free run) sums the taps that
+// share a coefficient id AND a z offset (COMM/ASSOC, ascending address) and
+// multiplies once with an FMA (FMA1).
 #include "generic_body.hpp"
 #include "internal.hpp"
 #include "rtc.hpp"
@@ -52,53 +54,62 @@ __global__ void generic_plain(const T *__restrict__ src, T *__restrict__ dst, Ge
 }
 
 // Table-driven tap sums: slot s's groups are read from the plan's tables.
-template <typename T, int R, int TX, int TY, bool CORNERS>
-struct TableSlotsW {
+template <int R, int W, int RY>
+struct TableSlots {
+    static constexpr bool rotate = false;
     GenTab tab;
-    __device__ __forceinline__ void operator()(const double *__restrict__ t, int me, double *acc) const {
-        constexpr int W = TX + 2 * R;
+    template <int>
+    __device__ __forceinline__ void add(const double *__restrict__ t, int me, unsigned live, double (*acc)[RY]) const {
 #pragma unroll
         for (int s = 0; s < 2 * R + 1; ++s) {
+            if (!(live >> s & 1)) continue;
             const int g0 = tab.slot_g[s], g1 = tab.slot_g[s + 1];
-            double a = acc[s];
+            double a[RY];
+#pragma unroll
+            for (int m = 0; m < RY; ++m) a[m] = acc[s][m];
             for (int gi = g0; gi < g1; ++gi) {
                 const int t0 = tab.g_t[gi], t1 = tab.g_t[gi + 1];
-                // the group's taps (ascending address): eight LDS reads in
-                // flight, four independent partial sums, then one FMA
-                double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-                int ti = t0;
-                for (; ti + 8 <= t1; ti += 8) {
-                    double v[8];
+                // the group's taps (ascending address): alternately into two
+                // partial sums per row, then one FMA
+                double s0[RY], s1[RY];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        const int xy = tab.t_xy[ti + q];
-                        v[q] = t[me + (xy >> 16) * W + (short)(xy & 0xFFFF)];
+                for (int m = 0; m < RY; ++m) s0[m] = s1[m] = 0.0;
+                int ti = t0;
+                for (; ti + 2 <= t1; ti += 2) {
+                    const int xa = tab.t_xy[ti], xb = tab.t_xy[ti + 1];
+                    const double *pa = t + me + (xa >> 16) * W + (short)(xa & 0xFFFF);
+                    const double *pb = t + me + (xb >> 16) * W + (short)(xb & 0xFFFF);
+#pragma unroll
+                    for (int m = 0; m < RY; ++m) {
+                        s0[m] += pa[m * W];
+                        s1[m] += pb[m * W];
                     }
-                    s0 += v[0] + v[4];
-                    s1 += v[1] + v[5];
-                    s2 += v[2] + v[6];
-                    s3 += v[3] + v[7];
                 }
-                for (; ti < t1; ++ti) {
-                    const int xy = tab.t_xy[ti];
-                    s0 += t[me + (xy >> 16) * W + (short)(xy & 0xFFFF)];
+                if (ti < t1) {
+                    const int xa = tab.t_xy[ti];
+                    const double *pa = t + me + (xa >> 16) * W + (short)(xa & 0xFFFF);
+#pragma unroll
+                    for (int m = 0; m < RY; ++m) s0[m] += pa[m * W];
                 }
-                a = fma(tab.g_c[gi], (s0 + s1) + (s2 + s3), a);
+#pragma unroll
+                for (int m = 0; m < RY; ++m) a[m] = fma(tab.g_c[gi], s0[m] + s1[m], a[m]);
             }
-            acc[s] = a;
+#pragma unroll
+            for (int m = 0; m < RY; ++m) acc[s][m] = a[m];
         }
     }
 };
 
-template <typename T, int R, int TX, int TY, bool CORNERS>
-__global__ __launch_bounds__(TX *TY) void generic_sat(const T *__restrict__ src, T *__restrict__ dst, Geom g,
+template <typename T, int R, int TX, int BY, int RY, bool CORNERS>
+__global__ __launch_bounds__(TX *BY) void generic_sat(const T *__restrict__ src, T *__restrict__ dst, Geom g,
                                                       GenTab tab, int zb, int remap, double *__restrict__ part) {
-    __shared__ double tile[2][(TY + 2 * R) * (TX + 2 * R)];
+    constexpr int W = TX + 2 * R;
+    __shared__ double tile[2][(BY * RY + 2 * R) * W];
     __shared__ double red[kMaxWaves];
     int bx, by, bz;
     tile_coords(remap, bx, by, bz);
-    const double sacc = generic_sat_body<T, R, TX, TY, CORNERS>(src, dst, g, zb, bx, by, bz,
-                                                               TableSlotsW<T, R, TX, TY, CORNERS>{tab}, tile);
+    const double sacc = generic_rows_body<T, R, TX, BY, RY, CORNERS, unsigned long long>(
+        src, dst, g, zb, bx, by, bz, part != nullptr, TableSlots<R, W, RY>{tab}, tile);
     if (part) {
         const double s = block_sum_f64(sacc, red);
         if (threadIdx.x == 0 && threadIdx.y == 0) part[block_linear_id()] = s;
@@ -110,12 +121,14 @@ bool plain_tile_ok(Tile t) {
     return t.tx >= 1 && t.ty >= 1 && t.tz >= 1 && n % 64 == 0 && n <= 1024;
 }
 
-#define GEN_SAT_TILES(X) X(32, 4) X(32, 8) X(64, 2) X(64, 4) X(128, 2)
+// Saturated tiles: (TX, tile rows) -> thread rows BY, rows per thread RY
+#define GEN_SAT_TILES(X) X(32, 4, 2, 2) X(32, 8, 2, 4) X(64, 2, 1, 2) X(64, 4, 2, 2) X(128, 2, 1, 2) X(32, 16, 4, 4) \
+    X(32, 32, 8, 4) X(64, 16, 4, 4)
 
 bool gen_tile_ok(int v, Tile t) {
     if (v == V_PLAIN) return plain_tile_ok(t);
     if (t.tz < 1) return false;
-#define X(a, b) if (t.tx == a && t.ty == b) return true;
+#define X(a, b, by, ry) if (t.tx == a && t.ty == b) return true;
     GEN_SAT_TILES(X)
 #undef X
     return false;
@@ -123,11 +136,22 @@ bool gen_tile_ok(int v, Tile t) {
 
 int gen_sat_tiles(Tile *out, int max) {
     int n = 0;
-#define X(a, b) if (n < max) out[n++] = Tile{a, b, 0};
+#define X(a, b, by, ry) if (n < max) out[n++] = Tile{a, b, 0};
     GEN_SAT_TILES(X)
 #undef X
     return n;
 }
+
+}  // namespace
+
+GenRows gen_rows(int tx, int ty) {
+#define X(a, b, by, ry) if (tx == a && ty == b) return {by, ry};
+    GEN_SAT_TILES(X)
+#undef X
+    return {0, 0};
+}
+
+namespace {
 
 long long gen_nblocks(int, Tile t, const Geom &g) { return cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, t.tz); }
 
@@ -141,10 +165,11 @@ hipError_t gen_launch_t(int v, Tile t, const SweepArgs &a, hipStream_t s) {
         return hipGetLastError();
     }
 #define GEN_LAUNCH(A_, B_, R_, C_)                                                                          \
-    hipLaunchKernelGGL((generic_sat<T, R_, A_, B_, C_>), grid, dim3(A_, B_, 1), 0, s, src, dst, a.g, a.gen,   \
+    hipLaunchKernelGGL((generic_sat<T, R_, A_, BY_, RY_, C_>), grid, dim3(A_, BY_, 1), 0, s, src, dst, a.g, a.gen, \
                        t.tz, a.remap, a.part)
-#define X(A, B)                                                                                             \
+#define X(A, B, BY, RY)                                                                                          \
     if (t.tx == A && t.ty == B) {                                                                           \
+        constexpr int BY_ = BY, RY_ = RY;                                                                   \
         const bool c = a.gen.corners;                                                                       \
         switch (a.g.r) {                                                                                    \
         case 1: if (c) GEN_LAUNCH(A, B, 1, true); else GEN_LAUNCH(A, B, 1, false); break;                               \

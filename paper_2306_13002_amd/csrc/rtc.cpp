@@ -45,53 +45,290 @@ unsigned long long fnv64(const std::string &s) {
     return h;
 }
 
-// Balanced-tree sum of LDS terms, in the given (ascending address) order.
-std::string tree(const std::vector<std::string> &terms, size_t a, size_t b) {
-    if (b - a == 1) return terms[a];
-    const size_t m = a + (b - a + 1) / 2;
-    return "(" + tree(terms, a, m) + " + " + tree(terms, m, b) + ")";
+// Emits one plane's contributions to the accumulator queue for every row of
+// a thread.  Values are named once and shared (the paper's common
+// subexpressions): a cell of the window is read from LDS once, a mirrored
+// pair u(-dx) + u(+dx) of a window row once for all the output rows that use
+// it, a pair of such rows (dy, -dy) and a whole group's sum once for all the
+// z slots whose groups have the same in-plane shape.
+struct SlotEmitter {
+    const RtcSpec &sp;
+    const int RY, W, phase;  // phase: see generic_rows_body
+    std::string o;
+    std::map<std::string, std::string> memo;  // expression -> name
+    int n_add = 0, n_fma = 0, n_name = 0;
+
+    SlotEmitter(const RtcSpec &sp_, int ry, int w, int ph) : sp(sp_), RY(ry), W(w), phase(ph) {}
+
+    std::string named(const std::string &expr) {
+        auto it = memo.find(expr);
+        if (it != memo.end()) return it->second;
+        const std::string nm = "v" + std::to_string(n_name++);
+        o += "        const double " + nm + " = " + expr + ";\n";
+        return memo[expr] = nm;
+    }
+    std::string add(const std::string &a, const std::string &b) {
+        const std::string expr = a + " + " + b;
+        if (!memo.count(expr)) ++n_add;
+        return named(expr);
+    }
+    // cell dx of window row wy (row m of the thread is window row m + R)
+    std::string cell(int dx, int wy) { return named("t[me + " + std::to_string((wy - sp.R) * W + dx) + "]"); }
+    std::string tree(const std::vector<std::string> &v, size_t a, size_t b) {
+        if (b - a == 1) return v[a];
+        const size_t m = a + (b - a + 1) / 2;
+        const std::string l = tree(v, a, m);
+        return add(l, tree(v, m, b));
+    }
+    // the sum of a group's taps for output row m
+    std::string sum(const RtcGroup &gr, int m) {
+        const int R = sp.R, w = 2 * R + 1;
+        std::vector<int> has(w * w, 0);
+        for (const auto &t : gr.taps) has[(t.second + R) * w + t.first + R]++;
+        // per row dy: mirrored pairs, then single cells (a tap named twice counts twice)
+        std::vector<std::string> terms;
+        auto item = [&](int kind, int dx, int dy) {  // kind 1: the pair of |dx|, 0: one cell
+            const int wy = m + R + dy;
+            if (!kind) return cell(dx, wy);
+            const std::string l = cell(-dx, wy);
+            return add(l, cell(dx, wy));
+        };
+        std::vector<std::pair<int, int>> rows[9];  // dy + R -> (kind, dx)
+        for (int dy = -R; dy <= R; ++dy) {
+            int *h = &has[(dy + R) * w];
+            for (int dx = R; dx >= 1; --dx)
+                while (h[R + dx] > 0 && h[R - dx] > 0) {
+                    rows[dy + R].push_back({1, dx});
+                    --h[R + dx];
+                    --h[R - dx];
+                }
+            for (int dx = -R; dx <= R; ++dx)
+                for (; h[R + dx] > 0; --h[R + dx]) rows[dy + R].push_back({0, dx});
+        }
+        for (int dy = 0; dy <= R; ++dy) {
+            std::vector<std::pair<int, int>> up = rows[R + dy], dn = dy ? rows[R - dy] : std::vector<std::pair<int, int>>();
+            for (const auto &it : up) {
+                auto f = std::find(dn.begin(), dn.end(), it);
+                if (f != dn.end()) {
+                    dn.erase(f);
+                    const std::string l = item(it.first, it.second, -dy);
+                    terms.push_back(add(l, item(it.first, it.second, dy)));
+                } else {
+                    terms.push_back(item(it.first, it.second, dy));
+                }
+            }
+            for (const auto &it : dn) terms.push_back(item(it.first, it.second, -dy));
+        }
+        return tree(terms, 0, terms.size());
+    }
+    static std::string lit(double c) {
+        char buf[48];
+        std::snprintf(buf, sizeof buf, "%a", c);
+        return buf;
+    }
+    // acc of slot s += c * v for row m (the queue starts each slot at 0)
+    void fma_into(int s, int m, double c, const std::string &v) {
+        const int w = 2 * sp.R + 1;
+        const std::string dst = "acc[" + std::to_string((s - phase + w) % w) + "][" + std::to_string(m) + "]";
+        o += "        " + dst + " = fma(" + lit(c) + ", " + v + ", " + dst + ");\n";
+        ++n_fma;
+    }
+    bool guarded = false;  // skip the slots that are not live
+    void guard(int s) { o += guarded ? "        if (live >> " + std::to_string(s) + " & 1) {\n" : std::string("        {\n"); }
+    // The sums of every row first, shared among the slots, then slot by slot
+    // one FMA per group and row: for patterns whose sums repeat (a symmetric
+    // box adds and multiplies several times fewer values than it has taps).
+    void by_sums() {
+        const int NQ = 2 * sp.R + 1;
+        std::vector<std::vector<std::vector<std::string>>> v(NQ, std::vector<std::vector<std::string>>(RY));
+        for (int m = 0; m < RY; ++m)
+            for (int s = 0; s < NQ; ++s)
+                for (const RtcGroup &gr : sp.slots[s]) v[s][m].push_back(sum(gr, m));
+        for (int s = 0; s < NQ; ++s) {
+            if (sp.slots[s].empty()) continue;
+            guard(s);
+            for (size_t g = 0; g < sp.slots[s].size(); ++g)
+                for (int m = 0; m < RY; ++m) fma_into(s, m, sp.slots[s][g].coef, v[s][m][g]);
+            o += "        }\n";
+        }
+    }
+    // Column by column of the window, one FMA per tap, each coefficient used
+    // for all the thread's rows at once: for patterns whose sums do not repeat.
+    void by_taps() {
+        const int R = sp.R, w = 2 * R + 1, NQ = 2 * R + 1;
+        std::vector<std::vector<std::vector<double>>> c(NQ, std::vector<std::vector<double>>(w * w));
+        for (int s = 0; s < NQ; ++s)
+            for (const RtcGroup &gr : sp.slots[s])
+                for (const auto &t : gr.taps) c[s][(t.second + R) * w + t.first + R].push_back(gr.coef);
+        for (int dx = 0; dx < w; ++dx) {
+            for (int dy = 0; dy < w; ++dy)
+                for (int s = 0; s < NQ; ++s)
+                    for (int m = 0; m < RY && !c[s][dy * w + dx].empty(); ++m) cell(dx - R, m + dy);
+            for (int s = 0; s < NQ; ++s) {
+                bool any = false;
+                for (int dy = 0; dy < w; ++dy)
+                    for (double v : c[s][dy * w + dx]) {
+                        if (!any) guard(s);
+                        any = true;
+                        for (int m = 0; m < RY; ++m) fma_into(s, m, v, cell(dx - R, m + dy));
+                    }
+                if (any) o += "        }\n";
+            }
+        }
+    }
+};
+
+}  // namespace
+
+namespace {
+
+// How a stencil's plane arithmetic is emitted for RY rows per thread.
+struct EmitPlan {
+    int ry;
+    bool share;     // group sums shared among the slots (by_sums), else one FMA per tap (by_taps)
+    int per_plane;  // FP64 instructions per thread and plane
+    bool rotate;    // the accumulator queue moves on by name
+    bool guarded;   // slots that are not live are skipped
+};
+
+// What a kernel's source depends on besides its tile, as text.
+const std::string &spec_key(RtcSpec &sp) {
+    if (!sp.key.empty()) return sp.key;
+    std::string k;
+    auto put = [&k](const void *v, size_t n) { k.append((const char *)v, n); };
+    const int head[3] = {sp.R, sp.eb, sp.corners};
+    put(head, sizeof head);
+    put(&sp.row_bytes, sizeof sp.row_bytes);
+    for (const auto &sl : sp.slots) {
+        const int n = (int)sl.size();
+        put(&n, sizeof n);
+        for (const RtcGroup &g : sl) {
+            const int m = (int)g.taps.size();
+            put(&g.coef, sizeof g.coef);
+            put(&m, sizeof m);
+            for (const auto &t : g.taps) {
+                put(&t.first, sizeof t.first);
+                put(&t.second, sizeof t.second);
+            }
+        }
+    }
+    return sp.key = k;
+}
+
+// Per stencil of the process: how it is emitted, and its kernels per tile and
+// device.  A plan of a stencil that another plan has compiled takes both from
+// here instead of emitting the source again (0.3 to 3 ms).  Entries stay as
+// long as the modules do, and there are no more of them.
+struct SpecEntry {
+    std::vector<EmitPlan> emit;
+    std::map<std::vector<int>, hipFunction_t> fn;  // tx, ty, device
+};
+std::map<std::string, SpecEntry> g_specs;  // guarded by g_mu
+
+EmitPlan emit_plan(RtcSpec &sp, int ry) {
+    const std::string &key = spec_key(sp);
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto it = g_specs.find(key);
+        if (it != g_specs.end())
+            for (const EmitPlan &e : it->second.emit)
+                if (e.ry == ry) return e;
+    }
+    int taps = 0;
+    for (const auto &sl : sp.slots)
+        for (const RtcGroup &g : sl) taps += (int)g.taps.size();
+    SlotEmitter er(sp, ry, 1024, 0);
+    er.by_sums();
+    EmitPlan p;
+    p.ry = ry;
+    // The shared sums win where they save at least a tenth of one FMA per tap
+    // (a symmetric box of radius 3: 100 instead of 343 instructions per point).
+    p.share = 10 * (er.n_add + er.n_fma) <= 9 * ry * taps;
+    p.per_plane = p.share ? er.n_add + er.n_fma : ry * taps;
+    // The rotating queue repeats the plane's arithmetic 2R+1 times: taken up
+    // to 4096 FP64 instructions (32 KB of the 64 KB instruction cache).
+    p.rotate = p.per_plane * (2 * sp.R + 1) <= 4096;
+    // Skipping pays from about 64 instructions per point on (box r = 2, 125
+    // coefficients: 81 -> 64 us a sweep at 201 x 233 x 160); the branches cost
+    // small stencils more (star r = 1 at 64^3: 8.4 -> 10.4 us).
+    p.guarded = p.per_plane >= 64 * ry;
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_specs[key].emit.push_back(p);
+    return p;
 }
 
 }  // namespace
 
-std::string rtc_generic_source(const RtcSpec &sp, int TX, int TY) {
-    const int R = sp.R, W = TX + 2 * R;
-    std::string o;
-    char buf[256];
-    o += "#include \"generic_body.hpp\"\n\nnamespace {\nstruct GenSlots {\n";
-    o += "    __device__ __forceinline__ void operator()(const double *__restrict__ t, int me, double *acc) const {\n";
-    o += "        double a;\n";
-    for (int s = 0; s < 2 * R + 1; ++s) {
-        if (sp.slots[s].empty()) continue;
-        std::snprintf(buf, sizeof buf, "        a = acc[%d];\n", s);
-        o += buf;
-        for (const RtcGroup &gr : sp.slots[s]) {
-            std::vector<std::string> terms;
-            for (const auto &xy : gr.taps) {
-                std::snprintf(buf, sizeof buf, "t[me + %d]", xy.second * W + xy.first);
-                terms.push_back(buf);
-            }
-            std::snprintf(buf, sizeof buf, "%a", gr.coef);
-            o += "        a = fma(" + std::string(buf) + ", " + tree(terms, 0, terms.size()) + ", a);\n";
+// Default tile of a generated kernel.  32 lanes along x where they leave at
+// least 7 % fewer lanes outside the grid than 64 do, 16 rows, and the z-block
+// with the lowest estimate of
+//   [live planes * 4.7 FP64 + planes * 600] * (waves per SIMD + 0.7)  cycles:
+// 4.7 cycles per FP64 instruction as measured, 600 for staging a plane and
+// its LDS reads, 0.7 for what a block's barriers leave idle.  Small z-blocks
+// give more waves, large ones fewer planes that are loaded only for their
+// neighbours.  Measured us per sweep at z-blocks 4 / 8 / 16 / 32, the pick in
+// brackets: box r = 3 f64 symmetric 256^3 172 / 133 / 117 / [106]; box r = 2
+// f32 201 x 233 x 160 58 / [61] / 73 / 109; star r = 4 f32 321 x 190 x 257
+// 97 / 69 / [59] / 61; box r = 3 f64 128 x 130 x 140 [59] / 75 / 97 / 179.
+// With 64 x 4 tiles, one row per thread and z-blocks of 16 (the default
+// before) these took 163, 93, 94 and 89.
+Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
+    Tile t{64, 16, 4};
+    if (100 * cdiv(g.nx, 32) * 32 <= 93 * cdiv(g.nx, 64) * 64) t.tx = 32;
+    const GenRows gr = gen_rows(t.tx, t.ty);
+    const EmitPlan ep = emit_plan(sp, gr.ry);
+    const double waves = t.tx * gr.by / 64.0, fp = 4.7 * ep.per_plane;
+    double best = 0;
+    for (int zb : {2, 4, 8, 16, 32, 64}) {
+        if (zb > 2 && zb >= 2 * g.nz) break;
+        const double per_cu = (double)cdiv(cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, zb), 256);
+        const double planes = zb + 2 * sp.R, live = ep.guarded && !ep.share ? zb : planes;
+        const double est = (live * fp + planes * 600) * (per_cu * waves / 4 + 0.7);
+        if (zb == 2 || est < best) {
+            best = est;
+            t.tz = zb;
         }
-        std::snprintf(buf, sizeof buf, "        acc[%d] = a;\n", s);
-        o += buf;
+    }
+    return t;
+}
+
+std::string rtc_generic_source(RtcSpec &sp, int TX, int TY) {
+    const int R = sp.R, W = TX + 2 * R;
+    const GenRows gr = gen_rows(TX, TY);
+    const EmitPlan ep = emit_plan(sp, gr.ry);
+    std::string o;
+    char buf[320];
+    o += "#include \"generic_body.hpp\"\n\nnamespace {\nstruct GenSlots {\n    static constexpr bool rotate = ";
+    o += ep.rotate ? "true;\n" : "false;\n";
+    std::snprintf(buf, sizeof buf,
+                  "    template <int PH>\n    __device__ __forceinline__ void add(const double *__restrict__ t, int me, "
+                  "unsigned live, double (*acc)[%d]) const {\n",
+                  gr.ry);
+    o += buf;
+    for (int ph = 0; ph < (ep.rotate ? 2 * R + 1 : 1); ++ph) {
+        SlotEmitter em(sp, gr.ry, W, ph);
+        em.guarded = ep.guarded;
+        if (ep.share) em.by_sums();
+        else em.by_taps();
+        std::snprintf(buf, sizeof buf, "        if constexpr (PH == %d) {\n", ph);
+        o += buf + em.o + "        }\n";
     }
     o += "    }\n};\n}  // namespace\n\n";
     const char *T = sp.eb == 4 ? "float" : "double";
     std::snprintf(buf, sizeof buf,
                   "extern \"C\" __global__ __launch_bounds__(%d) void stencil_generic_gen(const %s *__restrict__ src, "
                   "%s *__restrict__ dst, stn::Geom g, int zb, int remap, double *__restrict__ part) {\n",
-                  TX * TY, T, T);
+                  TX * gr.by, T, T);
     o += buf;
     std::snprintf(buf, sizeof buf, "    __shared__ double tile[2][%d];\n    __shared__ double red[16];\n",
                   (TY + 2 * R) * W);
     o += buf;
     o += "    int bx, by, bz;\n    stn::tile_coords(remap, bx, by, bz);\n";
     std::snprintf(buf, sizeof buf,
-                  "    const double sacc = stn::generic_sat_body<%s, %d, %d, %d, %s>(src, dst, g, zb, bx, by, bz, "
-                  "GenSlots{}, tile);\n",
-                  T, R, TX, TY, sp.corners ? "true" : "false");
+                  "    const double sacc = stn::generic_rows_body<%s, %d, %d, %d, %d, %s, %s>(src, dst, g, zb, bx, by, bz, "
+                  "part != nullptr, GenSlots{}, tile);\n",
+                  T, R, TX, gr.by, gr.ry, sp.corners ? "true" : "false",
+                  (TY + 2 * R) * sp.row_bytes < 0xFFFFFFF0LL ? "unsigned" : "unsigned long long");
     o += buf;
     o += "    if (part) {\n        const double s = stn::block_sum_f64(sacc, red);\n";
     o += "        if (threadIdx.x == 0 && threadIdx.y == 0) part[stn::block_linear_id()] = s;\n    }\n}\n";
@@ -170,33 +407,56 @@ hipFunction_t rtc_function(const std::string &src, const char *kernel) {
     return fn;
 }
 
-static hipFunction_t get_kernel(const RtcSpec &sp, int TX, int TY) {
-    return rtc_function(rtc_generic_source(sp, TX, TY), "stencil_generic_gen");
-}
-
-bool rtc_prepare(const RtcSpec &sp, const std::vector<Tile> &tiles) {
+bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles) {
     // compile the distinct tiles concurrently
     std::vector<Tile> uniq;
     for (const Tile &t : tiles) {
         bool seen = false;
         for (const Tile &u : uniq) seen |= (u.tx == t.tx && u.ty == t.ty);
+        for (const RtcSpec::Kernel &k : sp.kernels) seen |= (k.tx == t.tx && k.ty == t.ty);
         if (!seen) uniq.push_back(t);
     }
-    std::vector<char> ok(uniq.size(), 0);
+    std::vector<hipFunction_t> fn(uniq.size(), nullptr);
     int dev = 0;
     (void)hipGetDevice(&dev);
+    const std::string &key = spec_key(sp);
+    auto at = [&](size_t i) { return std::vector<int>{uniq[i].tx, uniq[i].ty, dev}; };
+    std::vector<size_t> todo;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        const SpecEntry &e = g_specs[key];
+        for (size_t i = 0; i < uniq.size(); ++i) {
+            auto it = e.fn.find(at(i));
+            if (it != e.fn.end()) fn[i] = it->second;
+            else todo.push_back(i);
+        }
+    }
+    auto compile = [&](size_t i) {
+        fn[i] = rtc_function(rtc_generic_source(sp, uniq[i].tx, uniq[i].ty), "stencil_generic_gen");
+    };
     std::vector<std::thread> th;
-    for (size_t i = 0; i < uniq.size(); ++i)
-        th.emplace_back([&, i] {
+    for (size_t k = 1; k < todo.size(); ++k)
+        th.emplace_back([&, k] {
             (void)hipSetDevice(dev);
-            ok[i] = get_kernel(sp, uniq[i].tx, uniq[i].ty) != nullptr;
+            compile(todo[k]);
         });
+    if (!todo.empty()) compile(todo[0]);
     for (auto &t : th) t.join();
-    return std::all_of(ok.begin(), ok.end(), [](char c) { return c != 0; });
+    bool ok = true;
+    std::lock_guard<std::mutex> lk(g_mu);
+    for (size_t i = 0; i < uniq.size(); ++i) {
+        ok &= fn[i] != nullptr;
+        if (!fn[i]) continue;
+        g_specs[key].fn[at(i)] = fn[i];
+        sp.kernels.push_back({uniq[i].tx, uniq[i].ty, fn[i]});
+    }
+    return ok;
 }
 
 hipError_t rtc_generic_launch(const RtcSpec &sp, Tile t, const SweepArgs &a, hipStream_t s) {
-    hipFunction_t fn = get_kernel(sp, t.tx, t.ty);
+    hipFunction_t fn = nullptr;
+    for (const RtcSpec::Kernel &k : sp.kernels)
+        if (k.tx == t.tx && k.ty == t.ty) fn = k.fn;
     if (!fn) return hipErrorInvalidImage;
     const void *src = a.src;
     void *dst = a.dst;
@@ -205,7 +465,7 @@ hipError_t rtc_generic_launch(const RtcSpec &sp, Tile t, const SweepArgs &a, hip
     double *part = a.part;
     void *args[] = {&src, &dst, &g, &zb, &remap, &part};
     return hipModuleLaunchKernel(fn, (unsigned)cdiv(a.g.nx, t.tx), (unsigned)cdiv(a.g.ny, t.ty),
-                                 (unsigned)cdiv(a.g.nz, t.tz), t.tx, t.ty, 1, 0, s, args, nullptr);
+                                 (unsigned)cdiv(a.g.nz, t.tz), t.tx, gen_rows(t.tx, t.ty).by, 1, 0, s, args, nullptr);
 }
 
 }  // namespace stn

@@ -20,16 +20,38 @@ struct RtcGroup {
 struct RtcSpec {
     int R = 1, eb = 8;
     bool corners = false;
+    long long row_bytes = 0;  // row pitch in bytes
     std::vector<std::vector<RtcGroup>> slots;  // 2R+1 slots, slot s holds dz = s - R
+    // The plan's compiled kernels, by tile: a launch takes its kernel from
+    // here.  (Emitting and hashing the source on each launch cost 90 us and
+    // more, longer than most sweeps.)
+    // ... and the text that identifies the stencil among the process's plans
+    // (made by the first use)
+    std::string key;
+    struct Kernel {
+        int tx, ty;
+        hipFunction_t fn;
+    };
+    std::vector<Kernel> kernels;
 };
+
+// Thread rows (by) and rows per thread (ry) of a generated kernel's tile;
+// by * ry = tile rows.
+struct GenRows {
+    int by, ry;
+};
+GenRows gen_rows(int tx, int ty);
 
 // Compile (or fetch from the in-process and STENCIL_RTC_CACHE caches) kernel
 // `kernel` of `src` for the current device; nullptr (error text set) on failure.
 hipFunction_t rtc_function(const std::string &src, const char *kernel);
 
-std::string rtc_generic_source(const RtcSpec &sp, int TX, int TY);
-// Compile the generated kernels of the given tiles (concurrently); false if any failed.
-bool rtc_prepare(const RtcSpec &sp, const std::vector<Tile> &tiles);
+// The tile a plan takes when its descriptor leaves it open (FIXED tuning).
+Tile rtc_default_tile(RtcSpec &sp, const Geom &g);
+std::string rtc_generic_source(RtcSpec &sp, int TX, int TY);
+// Compile the generated kernels of the given tiles (concurrently) and keep
+// them in sp.kernels; false if any failed.
+bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles);
 hipError_t rtc_generic_launch(const RtcSpec &sp, Tile t, const SweepArgs &a, hipStream_t s);
 
 }  // namespace stn

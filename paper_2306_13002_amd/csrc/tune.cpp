@@ -138,9 +138,9 @@ std::vector<Cand> tune_candidates(const KindOps *ops, int kind, const Geom &g, c
         const int ns = ops->sat_tiles(st, 64);
         std::vector<int> zbs;
         if (kind == STENCIL_GENERIC) {
-            // pruned: generic kernels re-read no plane, so z depth only trades
-            // priming against block count
-            for (int zb : {16, 64})
+            // z depth trades planes loaded for their neighbours only against
+            // block count
+            for (int zb : {4, 8, 16, 32, 64})
                 if (zb < g.nz) zbs.push_back(zb);
         } else {
             for (int zb : kZblocks)
@@ -176,11 +176,12 @@ struct Buffers {
 
 std::string tune_key(const stencil_plan_s *p, const TuneRequest &rq) {
     char buf[512];
-    // "/c7": candidate set 7 (AUTO includes the two- and three-sweep forms,
+    // "/c8": candidate set 8 (AUTO includes the two- and three-sweep forms,
     // the latter with intermediate z-blocks; HEAT2D5 the fused plain sweeps
-    // with one-cell-per-thread tiles; the closest candidates re-timed); entries
-    // of earlier sets are not reused
-    std::snprintf(buf, sizeof buf, "k%d/d%d/bc%d/n%dx%dx%d/r%d/py%lld/pz%lld/v%d/t%d,%d,%d,%d/h%08x/c7", p->kind,
+    // with one-cell-per-thread tiles; GENERIC tiles of 16 and 32 rows and
+    // z-blocks from 4; the closest candidates re-timed); entries of earlier
+    // sets are not reused
+    std::snprintf(buf, sizeof buf, "k%d/d%d/bc%d/n%dx%dx%d/r%d/py%lld/pz%lld/v%d/t%d,%d,%d,%d/h%08x/c8", p->kind,
                   p->dtype, p->bc, p->g.nx, p->g.ny, p->g.nz, p->g.r, p->g.py, p->g.pz, rq.variant, rq.tile_x,
                   rq.tile_y, rq.zblock, rq.tile_map, p->taps_hash);
     return buf;
