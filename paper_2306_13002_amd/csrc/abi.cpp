@@ -296,7 +296,12 @@ long long span_elems(const stencil_plan_s *p) {
 
 stencil_status alloc_plan_buffers(stencil_plan_s *p) {
     hipError_t e;
-    p->nblocks = p->ops->nblocks(p->variant, p->tile, p->g);
+    // launches as reported unless the plan's defaults run others
+    for (Launch *l : {&p->one, &p->many}) {
+        if (l->tile.tx == 0) *l = Launch{p->variant, p->tile, p->remap};
+        l->nblocks = p->ops->nblocks(l->variant, l->tile, p->g);
+    }
+    p->nblocks = std::max(p->one.nblocks, p->many.nblocks);
     if ((e = hipMalloc(&p->d_part, sizeof(double) * (size_t)p->nblocks)) != hipSuccess)
         return fail(STENCIL_E_NOMEM, "hipMalloc residual partials (%lld blocks): %s", p->nblocks, hipGetErrorString(e));
     if ((e = hipMalloc(&p->d_red, sizeof(double) * kReduceBlocks)) != hipSuccess)
@@ -351,6 +356,25 @@ struct DeviceGuard {
     }
 };
 
+// Launch shapes of a FIXED or MODEL plan whose descriptor leaves the tile open (the
+// plan reports its form's default shape).  Results are those of that form bit
+// for bit; the residual is the same sum taken in another order.
+//  - HEAT3D7 saturated forms run their register tiles (h3_default_tile).
+//  - AUTO lets the plan choose the form: runs of more than one sweep advance
+//    several per pass (HEAT3D7 three), which read and write the grid once
+//    (400^3, six sweeps: 1690 us single, 535 us by threes; 61 x 48 x 53, ten
+//    sweeps and the residual: 80 us in ten launches, 48 us in four).
+void default_launches(stencil_plan_s *p, int requested) {
+    const bool several = requested == STENCIL_AUTO && p->bc == STENCIL_BC_DIRICHLET;
+    if (p->kind == STENCIL_HEAT3D7 && p->variant != V_PLAIN) {
+        p->one = Launch{p->variant, h3_default_tile(p->variant, {p->g})};
+        p->many = several ? Launch{V_SAT3, h3_default_tile(V_SAT3, {p->g})} : p->one;
+    }
+}
+
+// The launch shape of a run of `iterations` sweeps.
+const Launch &run_launch(const stencil_plan_s *p, int iterations) { return iterations > 1 ? p->many : p->one; }
+
 stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
     const KindOps *ops = p->ops;
     bool has_sat = ops->sat_tiles != nullptr;
@@ -379,6 +403,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
             p->tile = e.tile;
             p->remap = e.remap;
             p->tuned = true;
+            if (!d->tile_x && !d->tile_y && !d->zblock) default_launches(p, e.variant);
             return STENCIL_OK;
         }
         if (st != STENCIL_E_STATE) return st;
@@ -397,6 +422,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
         p->tile = e.tile;
         p->remap = e.remap;
         p->tuned = true;
+        if (e.run_variant >= 0) p->one = p->many = Launch{e.run_variant, e.run_tile};
         return STENCIL_OK;
     }
     int v = dv;
@@ -416,6 +442,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
     p->variant = v;
     p->tile = t;
     p->remap = d->tile_map ? (d->tile_map == 2) : default_remap(p->kind);
+    if (!d->tile_x && !d->tile_y && !d->zblock) default_launches(p, dv);
     return STENCIL_OK;
 }
 
@@ -438,7 +465,6 @@ stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, co
     if (overlaps(fields[0], fields[1], span))
         return fail(STENCIL_E_INVAL, "fields[0] and fields[1] overlap (padded span %lld elements)", span_elems(p));
     a = p->base_args;
-    a.remap = p->remap;
     if (p->kind == STENCIL_POISSON19) {
         if (!coef_arrays) return fail(STENCIL_E_INVAL, "POISSON19 needs 12 coefficient arrays");
         for (int c = 0; c < 12; ++c) {
@@ -461,10 +487,10 @@ stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, co
 
 // The three parts of a run on stream s (enqueued eagerly or under capture).
 // Jacobi kinds first copy the state's halo into the scratch grid.
-hipError_t run_pre(stencil_plan_s *p, void *const *fields, hipStream_t s) {
+hipError_t run_pre(stencil_plan_s *p, void *const *fields, const Launch &l, hipStream_t s) {
     if (p->kind == STENCIL_WAVE25 || p->bc != STENCIL_BC_DIRICHLET) return hipSuccess;
     // fused HEAT2D5 sweeps write the scratch grid's boundary ring themselves
-    if (p->kind == STENCIL_HEAT2D5 && launch_sweeps(p->kind, p->variant, p->tile) > 1) return hipSuccess;
+    if (p->kind == STENCIL_HEAT2D5 && launch_sweeps(p->kind, l.variant, l.tile) > 1) return hipSuccess;
     return launch_halo_copy(fields[0], fields[1], elem_bytes(p->dtype), p->g, p->rz, s);
 }
 
@@ -473,8 +499,8 @@ hipError_t run_pre(stencil_plan_s *p, void *const *fields, hipStream_t s) {
 // two-sweep form advances two sweeps; an odd count starts with one single
 // saturated sweep at the same shape, so the last launch (the one that leaves
 // the residual partials) is always of the plan's form.
-hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int iterations, hipStream_t s,
-                      int *launches, double *part) {
+hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int iterations, const Launch &l,
+                      hipStream_t s, int *launches, double *part) {
     const bool wave = p->kind == STENCIL_WAVE25;
     const int eb = elem_bytes(p->dtype);
     void *src = wave ? fields[1] : fields[0], *dst = wave ? fields[0] : fields[1];
@@ -482,21 +508,22 @@ hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int i
     // one single-sweep launch); fused HEAT2D5 sweeps do tile.tz and the
     // three-sweep form three (the first launch takes the remainder of the
     // count)
-    const int per = launch_sweeps(p->kind, p->variant, p->tile);
-    const bool fused = (p->kind == STENCIL_HEAT2D5 && per > 1) || p->variant == V_SAT3;
+    const int per = launch_sweeps(p->kind, l.variant, l.tile);
+    const bool fused = (p->kind == STENCIL_HEAT2D5 && per > 1) || l.variant == V_SAT3;
     hipError_t e;
     *launches = 0;
     for (int t = 0; t < iterations;) {
         if (p->bc == STENCIL_BC_PERIODIC && (e = launch_periodic_fill(src, eb, p->g, p->rz, s)) != hipSuccess)
             return e;
         const int first = iterations % per;
-        const int v = (!fused && t == 0 && first) ? V_SATURATED : p->variant;
+        const int v = (!fused && t == 0 && first) ? V_SATURATED : l.variant;
         const int adv = fused ? (t == 0 && first ? first : per) : sweeps_per_launch(v);
         a.sweeps = adv;
+        a.remap = l.remap;
         a.src = src;
         a.dst = dst;
         a.part = (t + adv == iterations) ? part : nullptr;
-        if ((e = p->ops->launch(v, p->tile, a, s)) != hipSuccess) return e;
+        if ((e = p->ops->launch(v, l.tile, a, s)) != hipSuccess) return e;
         t += adv;
         ++*launches;
         std::swap(src, dst);
@@ -525,10 +552,11 @@ hipError_t capture_run(stencil_plan_s *p, void *const *fields, const SweepArgs &
         return e;
     }
     int launches = 0;
+    const Launch &l = run_launch(p, iterations);
     for (int part = 0; part < 3 && e == hipSuccess; ++part) {
         if ((e = hipStreamBeginCapture(rg->cap, hipStreamCaptureModeThreadLocal)) != hipSuccess) break;
-        const hipError_t le = part == 0 ? run_pre(p, fields, rg->cap)
-                              : part == 1 ? run_sweeps(p, fields, a, iterations, rg->cap, &launches, p->d_part)
+        const hipError_t le = part == 0 ? run_pre(p, fields, l, rg->cap)
+                              : part == 1 ? run_sweeps(p, fields, a, iterations, l, rg->cap, &launches, p->d_part)
                                           : run_post(p, fields, launches, rg->cap);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(rg->cap, &g);
@@ -608,7 +636,9 @@ stencil_status stencil_run(stencil_plan_t p, void *const *fields, const void *co
     if (!guard.ok) return fail(STENCIL_E_DEVICE, "cannot make device %d current", p->device);
     hipStream_t s = (hipStream_t)stream_;
     hipError_t e;
+    const Launch &l = run_launch(p, iterations);
     p->has_resid = false;
+    p->resid_blocks = l.nblocks;
     std::vector<const void *> sig{fields[0], fields[1]};
     const int ncoef = p->kind == STENCIL_POISSON19 ? 12 : (p->kind == STENCIL_WAVE25 ? 1 : 0);
     for (int c = 0; c < ncoef; ++c) sig.push_back(coef_arrays[c]);
@@ -642,10 +672,10 @@ stencil_status stencil_run(stencil_plan_t p, void *const *fields, const void *co
         }
         if (rg->x[2] && (e = hipGraphLaunch(rg->x[2], s)) != hipSuccess) return hip_fail(e, "hipGraphLaunch");
     } else {
-        if ((e = run_pre(p, fields, s)) != hipSuccess) return hip_fail(e, "halo copy launch");
+        if ((e = run_pre(p, fields, l, s)) != hipSuccess) return hip_fail(e, "halo copy launch");
         if (p->profiling && (e = hipEventRecord(p->ev0, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
         int launches = 0;
-        if ((e = run_sweeps(p, fields, a, iterations, s, &launches, p->d_part)) != hipSuccess)
+        if ((e = run_sweeps(p, fields, a, iterations, l, s, &launches, p->d_part)) != hipSuccess)
             return hip_fail(e, "sweep launch");
         if (p->profiling) {
             if ((e = hipEventRecord(p->ev1, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -669,9 +699,10 @@ stencil_status stencil_run_noalloc(stencil_plan_t p, void *const *fields, const 
     if (p->kind == STENCIL_GENERIC && p->variant == V_SATURATED && p->base_args.rtc)
         return fail(STENCIL_E_UNSUPPORTED, "generated GENERIC kernels are looked up by their source text at launch; "
                                            "the allocation-free run takes the table-driven kernel only");
-    if (p->nblocks > kNoallocPartials)
+    const Launch &l = run_launch(p, iterations);
+    if (l.nblocks > kNoallocPartials)
         return fail(STENCIL_E_UNSUPPORTED, "the plan's sweep launch has %lld blocks; the allocation-free run holds at most %lld",
-                    p->nblocks, kNoallocPartials);
+                    l.nblocks, kNoallocPartials);
     if (!fields) return fail(STENCIL_E_INVAL, "fields is NULL");
     if (iterations < 0) return fail(STENCIL_E_INVAL, "iterations < 0");
     if ((uintptr_t)residual_dev % alignof(double)) return fail(STENCIL_E_INVAL, "residual_dev is not 8-byte aligned");
@@ -685,12 +716,12 @@ stencil_status stencil_run_noalloc(stencil_plan_t p, void *const *fields, const 
     hipError_t e;
     double *scr = nullptr;
     if ((e = noalloc_scratch(&scr)) != hipSuccess) return hip_fail(e, "device scratch address");
-    if ((e = run_pre(p, fields, s)) != hipSuccess) return hip_fail(e, "halo copy launch");
+    if ((e = run_pre(p, fields, l, s)) != hipSuccess) return hip_fail(e, "halo copy launch");
     int launches = 0;
-    if ((e = run_sweeps(p, fields, a, iterations, s, &launches, scr)) != hipSuccess) return hip_fail(e, "sweep launch");
+    if ((e = run_sweeps(p, fields, a, iterations, l, s, &launches, scr)) != hipSuccess) return hip_fail(e, "sweep launch");
     if ((e = run_post(p, fields, launches, s)) != hipSuccess) return hip_fail(e, "tail copy launch");
     if (residual_dev &&
-        (e = launch_reduce_partials(scr, p->nblocks, scr + kNoallocPartials, residual_dev, s)) != hipSuccess)
+        (e = launch_reduce_partials(scr, l.nblocks, scr + kNoallocPartials, residual_dev, s)) != hipSuccess)
         return hip_fail(e, "reduce launch");
     return STENCIL_OK;
 }
@@ -703,7 +734,7 @@ stencil_status stencil_residual(stencil_plan_t p, double *host_out, void *stream
     hipStream_t s = (hipStream_t)stream_;
     if (p->batch) return batch_residuals(p, host_out, 1, s);
     hipError_t e;
-    if ((e = launch_reduce_partials(p->d_part, p->nblocks, p->d_red, p->h_result, s)) != hipSuccess)
+    if ((e = launch_reduce_partials(p->d_part, p->resid_blocks, p->d_red, p->h_result, s)) != hipSuccess)
         return hip_fail(e, "reduce launch");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     *host_out = *p->h_result;

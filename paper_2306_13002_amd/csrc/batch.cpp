@@ -142,8 +142,12 @@ stencil_status tune_class(const std::vector<int> &members, const std::vector<Geo
         local[k] = k;
         lg[k] = tg[members[k]];
     }
+    // the launches that give the same results as the candidates
+    std::vector<Cand> runs = run_candidates(STENCIL_HEAT3D7, geoms[big], r);
     size_t max_items = 0;
-    for (const Cand &c : cands) {
+    std::vector<Cand> all(cands);
+    all.insert(all.end(), runs.begin(), runs.end());
+    for (const Cand &c : all) {
         long long n = 0;
         for (const Geom &g : lg) n += cdiv(g.nx, c.tile.tx) * cdiv(g.ny, c.tile.ty) * cdiv(g.nz, c.tile.tz);
         max_items = std::max(max_items, (size_t)n);
@@ -209,6 +213,22 @@ stencil_status tune_class(const std::vector<int> &members, const std::vector<Geo
             bv.remap = 0;
         }
     }
+    double run_us = 1e300;
+    Cand run{};
+    for (const Cand &c : runs) {
+        double us = 0;
+        if ((e = time_cand(c, T, 3, &us)) != hipSuccess) return hip_fail(e, "class tuning launch");
+        logf("tune batch class (%d problems) launches v=%d tile=(%d,%d,%d): %.2f us/sweep", m, c.variant, c.tile.tx,
+             c.tile.ty, c.tile.tz, us);
+        if (us < run_us) {
+            run_us = us;
+            run = c;
+        }
+    }
+    if (run_us < bv.us) {
+        bv.run_variant = run.variant;
+        bv.run_tile = run.tile;
+    }
     if ((e = hipStreamSynchronize(sc.s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     *best = bv;
     return STENCIL_OK;
@@ -221,9 +241,9 @@ std::string class_key(const std::vector<int> &members, const std::vector<Geom> &
     for (int i : members)
         for (int v : {geoms[i].nx, geoms[i].ny, geoms[i].nz}) h = (h ^ (unsigned)v) * 16777619u;
     char buf[256];
-    // "/c7": the candidate set of single plans' set 7 (entries of earlier sets
+    // "/c8": the candidate set of single plans' set 8 (entries of earlier sets
     // are not reused)
-    std::snprintf(buf, sizeof buf, "batch/k%d/m%d/h%08x/v%d/t%d,%d,%d/c7", STENCIL_HEAT3D7, (int)members.size(), h,
+    std::snprintf(buf, sizeof buf, "batch/k%d/m%d/h%08x/v%d/t%d,%d,%d/c8", STENCIL_HEAT3D7, (int)members.size(), h,
                   rq.variant, rq.tile_x, rq.tile_y, rq.zblock);
     return buf;
 }
@@ -271,12 +291,12 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
         if ((e = hipStreamWaitEvent(s, b->evs[0], 0)) != hipSuccess) return abort_capture(e, "fork wait");
         // a two-sweep class starts an odd sweep count with one single sweep; a
         // three-sweep class starts with one launch of the remainder's sweeps
-        const int per = sweeps_per_launch(C.variant), rem = T % per;
+        const int cv = C.run.variant, per = sweeps_per_launch(cv), rem = T % per;
         for (int t = 0; t < T;) {
-            const int v = (t == 0 && rem && C.variant != V_SAT3) ? V_SATURATED : C.variant;
+            const int v = (t == 0 && rem && cv != V_SAT3) ? V_SATURATED : cv;
             const int adv = (t == 0 && rem) ? (v == V_SAT3 ? rem : 1) : sweeps_per_launch(v);
             double *part = (t + adv == T) ? b->d_part + C.item_base : nullptr;
-            if ((e = p->ops->batch_launch(v, C.tile, b->d_probs, b->d_items + C.item_base, C.n_items, launches[c] & 1,
+            if ((e = p->ops->batch_launch(v, C.run.tile, b->d_probs, b->d_items + C.item_base, C.n_items, launches[c] & 1,
                                           C.grid, adv, part, s)) != hipSuccess)
                 return abort_capture(e, "batch sweep");
             t += adv;
@@ -449,6 +469,7 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
             if (tuned) {
                 C.variant = te.variant;
                 C.tile = te.tile;
+                if (te.run_variant >= 0) C.run = Launch{te.run_variant, te.run_tile};
             }
         }
         if (!tuned) {
@@ -458,9 +479,18 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
             C.tile = rp->tile;
             free_plan(rp);
         }
+        if (C.run.tile.tx == 0) C.run = Launch{C.variant, C.tile};
+        if (!tuned && C.variant != V_PLAIN && !d.tile_x && !d.tile_y && !d.zblock) {
+            // the defaults' launches, as for single plans (default_launches),
+            // over the whole class: its problems fill the chip together
+            std::vector<Geom> gs;
+            for (int i : members) gs.push_back(geoms[i]);
+            C.run.variant = d.variant == STENCIL_AUTO ? V_SAT3 : C.variant;
+            C.run.tile = h3_default_tile(C.run.variant, gs);
+        }
         C.item_base = (int)items.size();
         std::vector<std::pair<int, int>> ranges;
-        std::vector<BatchItem> ci = class_items(members, geoms, C.tile, &ranges);
+        std::vector<BatchItem> ci = class_items(members, geoms, C.run.tile, &ranges);
         for (size_t k = 0; k < members.size(); ++k) {
             const int i = members[k];
             b->prob_class[i] = (int)b->classes.size();
@@ -470,8 +500,8 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
         C.n_items = (int)ci.size();
         C.grid = std::min(C.n_items, kBatchGrid);
         items.insert(items.end(), ci.begin(), ci.end());
-        logf("batch class %d: rep %d variant=%d tile=(%d,%d,%d) items=%d", c, rep[c], C.variant, C.tile.tx, C.tile.ty,
-             C.tile.tz, C.n_items);
+        logf("batch class %d: rep %d variant=%d tile=(%d,%d,%d) items=%d", c, rep[c], C.run.variant, C.run.tile.tx,
+             C.run.tile.ty, C.run.tile.tz, C.n_items);
         b->classes.push_back(C);
     }
     if (st != STENCIL_OK) {

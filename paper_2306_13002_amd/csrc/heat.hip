@@ -15,6 +15,9 @@
 // column lives in a three-deep register queue (each value loaded once), the
 // in-plane neighbours come from an LDS tile, and the next plane's loads are
 // all issued before the current plane is computed ("bulk load").
+#include <algorithm>
+#include <vector>
+
 #include "internal.hpp"
 
 namespace stn {
@@ -601,6 +604,175 @@ __global__ __launch_bounds__(RX *RY) void heat3d7_sat3(const double *__restrict_
     }
 }
 
+// Register tiles: KK sweeps per pass (1, 2 or 3) with the grid in registers.
+// A wave holds RY rows of 64 columns; NW waves stacked in y make a region of
+// 64 x RY*NW columns around the (64 - 2H) x (RY*NW - 2H) output tile, and the
+// block streams z.  At step p plane p arrives (loaded one step earlier) and
+// sweep j runs on plane p - j: its planes above and below are the thread's
+// own values, its x neighbours those of the next lanes (wave shifts), its y
+// neighbours the thread's own rows, and only the first and last row of each
+// wave pass through LDS (written at one step, read at the next, one barrier
+// per step).  Each sweep therefore costs a cell 7 FP64 instructions, 4 lane
+// moves and 2 selects, and an LDS access per two cells, where a tile in LDS
+// costs it five accesses; every cell is loaded once per block.  Sweep j is
+// right on the region less j rows and columns at its rim, so H >= KK.
+// Every value is computed with heat3d7_sat_tile's operations, so a pass
+// equals KK single-sweep launches bit for bit.  More sweeps than the last do
+// not cross the fixed boundary (rowm: the lanes of a row that are interior
+// cells; others keep their value).  Dirichlet only for KK > 1.
+//
+// Bound by issuing its vector instructions (three sweeps, 160^3: 164 per wave
+// and step, 70 % of the time at 4.5 cycles each; what is left is the step's
+// barrier) and, where the grid streams from HBM, by the rate of rows that
+// are not whole cache lines (a plain copy of 400^3 in this order: 210-250
+// us).  us per pass, LDS tiles at their defaults -> register tiles: three
+// sweeps 160^3 31.4 -> 20.4, 400^3 330 -> 253; one sweep 400^3 280 -> 233.
+// Deeper prefetch (2 or 3 planes), x neighbours through LDS, 8 rows per
+// thread and 4 to 6 sweeps per pass measured no better.
+__device__ __forceinline__ double lane_prev(double v) {  // lane i <- lane i - 1 (lane 0 <- 0)
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double lane_next(double v) {  // lane i <- lane i + 1 (lane 63 <- 0)
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xF, 0xF, true));
+}
+
+template <int H, int KK, int RY, int NW>
+struct H3Rt {
+    static_assert(KK >= 1 && KK <= H && H <= 3, "the rim is at least as wide as the sweeps are many");
+    static constexpr int TX = 64 - 2 * H, TY = RY * NW - 2 * H;
+    // first and last row of each wave, per sweep input and step parity
+    typedef double Edge[KK][2][NW][2][64];
+};
+
+template <int H, int KK, int RY, int NW>
+__device__ __forceinline__ double heat3d7_rt_tile(const double *__restrict__ src, double *__restrict__ dst,
+                                                  const Geom &g, double cc, double cn, int zb, int bx, int by, int bz,
+                                                  bool want_res, typename H3Rt<H, KK, RY, NW>::Edge &ex) {
+    constexpr int TX = H3Rt<H, KK, RY, NW>::TX, TY = H3Rt<H, KK, RY, NW>::TY;
+    const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int PX = g.nx + 2, PY = g.ny + 2;
+    const int X = bx * TX + 1 - H + lane, Y0 = by * TY + 1 - H + w * RY;  // padded coordinates of the first cell
+    const int k0 = bz * zb, k1 = min(k0 + zb, g.nz);                      // output planes k0+1 .. k1 (padded)
+    const int p0 = k0 + 1 - KK, pE = k1 + KK, pm = min(pE, g.nz + 1);
+    const bool outx = lane >= H && lane < 64 - H && X <= g.nx;
+    const unsigned xo = (unsigned)min(max(X, 0), PX - 1) * 8u, xs = outx ? (unsigned)X * 8u : 0u;
+    const unsigned long long inx = __ballot(X >= 1 && X <= g.nx);
+    const long long pzb = g.pz * 8, pyb = g.py * 8;
+    const int up = max(w - 1, 0), dn = min(w + 1, NW - 1);  // (the outermost rows read any value)
+    // uniform row pointers (rows outside the array: the nearest one, used by
+    // no cell that is needed)
+    const char *row[RY];
+    unsigned long long rowm[RY];
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        const int Y = Y0 + r;
+        row[r] = (const char *)(src + (long long)min(max(Y, 0), PY - 1) * g.py + (long long)max(p0, 0) * g.pz);
+        rowm[r] = Y >= 1 && Y <= g.ny ? inx : 0ull;
+    }
+    // L[j][s][r]: row r after j sweeps, at the plane in slot s = (plane - p0) mod 4
+    double L[KK][4][RY];
+#pragma unroll
+    for (int j = 0; j < KK; ++j)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int r = 0; r < RY; ++r) L[j][s][r] = 0.0;
+    auto load = [&](const int p, const int s) {  // plane p, clamped into what the block needs; then advance
+        const long long adv = p >= 0 && p < pm ? pzb : 0;
+#pragma unroll
+        for (int r = 0; r < RY; ++r) {
+            L[0][s][r] = buf_ld_f64(plane_rsrc(row[r]), xo);
+            row[r] += adv;
+        }
+    };
+    load(p0, 0);
+    const int r0 = max(0, H - w * RY), r1 = min(RY, min(H + TY - w * RY, g.ny - Y0 + 1));  // output rows
+    char *out = (char *)dst + ((long long)(k0 + 1) * g.pz + (long long)Y0 * g.py) * 8;
+    double acc = 0.0;
+    auto step = [&](const int p, const int u) {  // u = (p - p0) mod 4
+        const int par = u & 1;
+        load(p + 1, (u + 1) & 3);
+        double eu[KK], ed[KK];
+#pragma unroll
+        for (int j = 0; j < KK; ++j) {
+            eu[j] = ex[j][par ^ 1][up][1][lane];
+            ed[j] = ex[j][par ^ 1][dn][0][lane];
+        }
+        ex[0][par][w][0][lane] = L[0][u][0];
+        ex[0][par][w][1][lane] = L[0][u][RY - 1];
+#pragma unroll
+        for (int j = 1; j <= KK; ++j) {
+            const int q = p - j, c = (u + 4 - j) & 3, m = (u + 3 - j) & 3, a = (u + 5 - j) & 3;
+            double v[RY];
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                const double o = L[j - 1][c][r];
+                const double y0 = r == 0 ? eu[j - 1] : L[j - 1][c][r == 0 ? 0 : r - 1];
+                const double y1 = r == RY - 1 ? ed[j - 1] : L[j - 1][c][r == RY - 1 ? r : r + 1];
+                const double s = ((lane_prev(o) + lane_next(o)) + (y0 + y1)) + (L[j - 1][m][r] + L[j - 1][a][r]);
+                v[r] = fma(cn, s, cc * o);
+            }
+            if (j < KK) {
+                const unsigned long long zin = q >= 1 && q <= g.nz ? ~0ull : 0ull;
+#pragma unroll
+                for (int r = 0; r < RY; ++r)
+                    L[j < KK ? j : 0][c][r] = __builtin_amdgcn_inverse_ballot_w64(rowm[r] & zin) ? v[r] : L[j - 1][c][r];
+                ex[j < KK ? j : 0][par][w][0][lane] = L[j < KK ? j : 0][c][0];
+                ex[j < KK ? j : 0][par][w][1][lane] = L[j < KK ? j : 0][c][RY - 1];
+            } else if (p >= p0 + 2 * KK) {  // plane q = k0+1 and on
+                if (outx) {
+                    if (r0 == 0 && r1 == RY) {
+#pragma unroll
+                        for (int r = 0; r < RY; ++r) buf_st_f64(plane_rsrc(out + r * pyb), xs, v[r]);
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < RY; ++r)
+                            if (r >= r0 && r < r1) buf_st_f64(plane_rsrc(out + r * pyb), xs, v[r]);
+                    }
+                    if (want_res) {
+#pragma unroll
+                        for (int r = 0; r < RY; ++r)
+                            if (r >= r0 && r < r1) {
+                                const double d = v[r] - L[j - 1][c][r];
+                                acc = fma(d, d, acc);
+                            }
+                    }
+                }
+                out += pzb;
+            }
+        }
+        __syncthreads();
+    };
+    for (int p = p0;; p += 4) {
+        if (p > pE) break;
+        step(p, 0);
+        if (p + 1 > pE) break;
+        step(p + 1, 1);
+        if (p + 2 > pE) break;
+        step(p + 2, 2);
+        if (p + 3 > pE) break;
+        step(p + 3, 3);
+    }
+    return acc;
+}
+
+template <int H, int KK, int RY, int NW>
+__global__ __launch_bounds__(64 * NW) void heat3d7_rt(const double *__restrict__ src, double *__restrict__ dst, Geom g,
+                                                      double cc, double cn, int zb, int remap,
+                                                      double *__restrict__ part) {
+    __shared__ typename H3Rt<H, KK, RY, NW>::Edge ex;
+    __shared__ double red[kMaxWaves];
+    int bx, by, bz;
+    tile_coords(remap, bx, by, bz);
+    const double acc = heat3d7_rt_tile<H, KK, RY, NW>(src, dst, g, cc, cn, zb, bx, by, bz, part != nullptr, ex);
+    if (part) {
+        const double s = block_sum_f64(acc, red);
+        if (threadIdx.x == 0 && threadIdx.y == 0) part[block_linear_id()] = s;
+    }
+}
+
 // Work-list forms: each block walks items blockIdx.x, +gridDim.x, ... (the
 // batch launches one block per item up to 2^20 items) and runs the same tile
 // body as the single-problem kernel, so a batched problem is bit-identical to
@@ -659,6 +831,25 @@ __global__ __launch_bounds__(RX *RY) void heat3d7_sat3_batch(const BatchProb *__
         const BatchProb &Q = probs[w.prob];
         const double acc = heat3d7_sat3_tile<RX, RY, KK>(Q.f[parity], Q.f[parity ^ 1], Q.g, Q.cc, Q.cn, zb, w.bx,
                                                          w.by, w.bz, P, Lv);
+        if (part) {
+            const double s = block_sum_f64(acc, red);
+            if (threadIdx.x == 0 && threadIdx.y == 0) part[w.slot] = s;
+        }
+        __syncthreads();  // LDS is reused by the next item
+    }
+}
+
+template <int H, int KK, int RY, int NW>
+__global__ __launch_bounds__(64 * NW) void heat3d7_rt_batch(const BatchProb *__restrict__ probs,
+                                                            const BatchItem *__restrict__ items, int n_items,
+                                                            int parity, int zb, double *__restrict__ part) {
+    __shared__ typename H3Rt<H, KK, RY, NW>::Edge ex;
+    __shared__ double red[kMaxWaves];
+    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+        const BatchItem w = items[it];
+        const BatchProb &Q = probs[w.prob];
+        const double acc = heat3d7_rt_tile<H, KK, RY, NW>(Q.f[parity], Q.f[parity ^ 1], Q.g, Q.cc, Q.cn, zb, w.bx,
+                                                          w.by, w.bz, part != nullptr, ex);
         if (part) {
             const double s = block_sum_f64(acc, red);
             if (threadIdx.x == 0 && threadIdx.y == 0) part[w.slot] = s;
@@ -743,9 +934,49 @@ hipError_t h2_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
 // LDS.
 #define HEAT3D7_SAT3_REGIONS(X) X(32, 32) X(32, 24) X(32, 16) X(64, 16)
 
+// Register tiles: rim H, rows per thread RY, waves NW; output tile
+// (64 - 2H) x (RY*NW - 2H).  H = 3 runs up to three sweeps per launch, H = 2
+// two (or one, which starts an odd count), H = 1 one.
+#define HEAT3D7_RT1(X) X(1, 2, 4) X(1, 2, 8)
+#define HEAT3D7_RT2(X) X(2, 2, 8) X(2, 4, 8) X(2, 4, 12)
+#define HEAT3D7_RT3(X) X(3, 2, 8) X(3, 4, 8) X(3, 4, 12)
+#define RT_IS(h, ry, nw, t) ((t).tx == 64 - 2 * h && (t).ty == ry * nw - 2 * h)
+
+struct RtShape {
+    int h, ry, nw;
+};
+
+// Register tiles of a form.  They are what the defaults and the tuners launch
+// (and may be asked for), but not among the shapes plans report by themselves.
+// An odd count of a two-sweep plan starts
+// with one SATURATED launch of the same tile, so H = 2 tiles serve both.
+int h3_rt_shapes(int v, RtShape *out) {
+    int n = 0;
+#define X(h, ry, nw) out[n++] = RtShape{h, ry, nw};
+    if (v == V_SAT3) {
+        HEAT3D7_RT3(X)
+    } else if (v == V_SAT2) {
+        HEAT3D7_RT2(X)
+    } else if (v == V_SATURATED) {
+        HEAT3D7_RT1(X)
+        HEAT3D7_RT2(X)
+    }
+#undef X
+    return n;
+}
+
+bool h3_rt_tile(int v, Tile t) {
+    RtShape sh[8];
+    const int n = h3_rt_shapes(v, sh);
+    for (int i = 0; i < n; ++i)
+        if (RT_IS(sh[i].h, sh[i].ry, sh[i].nw, t)) return true;
+    return false;
+}
+
 bool h3_tile_ok(int v, Tile t) {
     if (v == V_PLAIN) return plain_tile_ok(t);
     if (t.tz < 1) return false;
+    if (h3_rt_tile(v, t)) return true;
     if (v == V_SAT3) {
 #define X(a, b) if (t.tx == a - 4 && t.ty == b - 4) return true;
         HEAT3D7_SAT3_REGIONS(X)
@@ -801,6 +1032,24 @@ hipError_t h3_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
                            a.part);
         return hipGetLastError();
     }
+    if (h3_rt_tile(v, t)) {
+        const int k = v == V_SAT3 ? a.sweeps : (v == V_SAT2 ? 2 : 1);
+#define GO(h, kk, ry, nw)                                                                                       \
+    hipLaunchKernelGGL((heat3d7_rt<h, kk, ry, nw>), grid, dim3(64, nw, 1), 0, s, src, dst, a.g, a.c[0], a.c[1], t.tz, \
+                       a.remap, a.part)
+#define X(h, ry, nw)                                                                                            \
+    if (RT_IS(h, ry, nw, t)) {                                                                                  \
+        if (k < 1 || k > h) return hipErrorInvalidValue;                                                        \
+        if (k == 1) GO(h, 1, ry, nw);                                                                           \
+        if constexpr (h >= 2) if (k == 2) GO(h, 2, ry, nw);                                                     \
+        if constexpr (h >= 3) if (k == 3) GO(h, 3, ry, nw);                                                     \
+        return hipGetLastError();                                                                               \
+    }
+        HEAT3D7_RT1(X) HEAT3D7_RT2(X) HEAT3D7_RT3(X)
+#undef X
+#undef GO
+        return hipErrorInvalidValue;
+    }
     if (v == V_SAT3) {
         if (a.sweeps < 1 || a.sweeps > 3) return hipErrorInvalidValue;
 #define X(A, B)                                                                                                \
@@ -844,6 +1093,24 @@ hipError_t h3_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
 
 hipError_t h3_batch_launch(int v, Tile t, const BatchProb *probs, const BatchItem *items, int n_items, int parity,
                            int grid, int sweeps, double *part, hipStream_t s) {
+    if (h3_rt_tile(v, t)) {
+        const int k = v == V_SAT3 ? sweeps : (v == V_SAT2 ? 2 : 1);
+#define GO(h, kk, ry, nw)                                                                                        \
+    hipLaunchKernelGGL((heat3d7_rt_batch<h, kk, ry, nw>), dim3(grid), dim3(64, nw, 1), 0, s, probs, items, n_items, parity, \
+                       t.tz, part)
+#define X(h, ry, nw)                                                                                            \
+    if (RT_IS(h, ry, nw, t)) {                                                                                  \
+        if (k < 1 || k > h) return hipErrorInvalidValue;                                                        \
+        if (k == 1) GO(h, 1, ry, nw);                                                                           \
+        if constexpr (h >= 2) if (k == 2) GO(h, 2, ry, nw);                                                     \
+        if constexpr (h >= 3) if (k == 3) GO(h, 3, ry, nw);                                                     \
+        return hipGetLastError();                                                                               \
+    }
+        HEAT3D7_RT1(X) HEAT3D7_RT2(X) HEAT3D7_RT3(X)
+#undef X
+#undef GO
+        return hipErrorInvalidValue;
+    }
     if (v == V_SAT3) {
         if (sweeps < 1 || sweeps > 3) return hipErrorInvalidValue;
 #define X(A, B)                                                                                                 \
@@ -891,6 +1158,57 @@ hipError_t h3_batch_launch(int v, Tile t, const BatchProb *probs, const BatchIte
 }
 
 }  // namespace
+
+// Default tile of a saturated form over one grid or the grids of a batch
+// class: the register tile and z-block with the lowest estimate of
+//   rounds * (planes + 2 sweeps) * cycles per step * (waves per SIMD + 0.7),
+// a step costing 4.5 cycles for each of 12.3 instructions per row and sweep
+// and 16 more; 0.7 is what the step's barrier leaves idle, once per round of
+// the blocks that are resident together (16 waves of a CU).  Measured us per
+// pass of three sweeps, tile and z-block as picked (others): 160^3 58x42x8
+// 20.4 (58x26x16 23.5, 58x42x16 28.2, 58x26x8 23.8); 54^3 58x10x2 6.5
+// (58x26x2 8.7, 58x10x8 9.4); 400^3 58x26x16 257 (x8 277, x32 270: the
+// blocks of a longer march drift apart, and rows at their borders leave
+// the L2 half written); 64 grids of edges 32 to 160, the largest class
+// 58x26x16 (326 us for all; 58x42x16 344, 58x26x8 355).  One sweep: 400^3 62x14x8 233 (x16 246, x32 268);
+// 54^3 62x14x2 3.2 (x8 4.8).
+Tile h3_default_tile(int v, const std::vector<Geom> &gs) {
+    RtShape sh[8];
+    const int n = h3_rt_shapes(v, sh), sweeps = sweeps_per_launch(v);
+    Tile best{64 - 2 * sh[0].h, sh[0].ry * sh[0].nw - 2 * sh[0].h, 8};
+    double cost = 0;
+    int deepest = 1;
+    for (const Geom &g : gs) deepest = std::max(deepest, g.nz);
+    for (int i = 0; i < n; ++i) {
+        if (v == V_SATURATED && sh[i].h != 1) continue;
+        const int tx = 64 - 2 * sh[i].h, ty = sh[i].ry * sh[i].nw - 2 * sh[i].h;
+        for (int zb : {2, 4, 8, 16, 32, 64, 128}) {
+            if (zb > 2 && zb >= 2 * deepest) break;
+            long long blocks = 0;
+            for (const Geom &g : gs) blocks += cdiv(g.nx, tx) * cdiv(g.ny, ty) * cdiv(g.nz, zb);
+            // longer marches only where the launch would have too many blocks
+            // for the allocation-free run
+            if (zb > (v == V_SATURATED ? 8 : 16) && blocks * 2 <= kNoallocPartials) break;
+            const double step = 4.5 * (12.3 * sh[i].ry * sweeps + 16);
+            const double per_cu = (double)cdiv(blocks, 256), res = std::min(per_cu, (double)(16 / sh[i].nw));
+            const double est = per_cu / res * (zb + 2 * sweeps) * step * (res * sh[i].nw / 4 + 0.7);
+            if (cost == 0 || est < cost) {
+                cost = est;
+                best = Tile{tx, ty, zb};
+            }
+        }
+    }
+    return best;
+}
+
+int h3_rt_tiles(int v, Tile *out) {
+    RtShape sh[8];
+    const int n = h3_rt_shapes(v, sh);
+    int k = 0;
+    for (int i = 0; i < n; ++i)
+        if (v != V_SATURATED || sh[i].h == 1) out[k++] = Tile{64 - 2 * sh[i].h, sh[i].ry * sh[i].nw - 2 * sh[i].h, 0};
+    return k;
+}
 
 KindOps heat2d5_ops = {h2_tile_ok, nullptr, nullptr, h2_nblocks, h2_launch, nullptr};
 KindOps heat3d7_ops = {h3_tile_ok, h3_sat_tiles, h3_sat2_tiles, h3_nblocks, h3_launch, h3_batch_launch, h3_sat3_tiles};

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "common.hpp"
 
 namespace stn {
@@ -82,6 +84,12 @@ struct KindOps {
                                int parity, int grid, int sweeps, double *part, hipStream_t s);
     int (*sat3_tiles)(Tile *out, int max);  // output tiles of the three-sweep form; nullptr if none
 };
+
+// HEAT3D7: default tile of a saturated form over one grid, or over the grids
+// of a batch class.
+Tile h3_default_tile(int variant, const std::vector<Geom> &gs);
+// The register tiles of a saturated form (at most 8; tz = 0).
+int h3_rt_tiles(int variant, Tile *out);
 
 extern KindOps heat2d5_ops, heat3d7_ops, poisson19_ops, wave25_ops, generic_ops;
 

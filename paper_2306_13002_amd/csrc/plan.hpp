@@ -11,9 +11,18 @@
 #include <vector>
 
 // Batched plan state (see batch.cpp).
-struct BatchClass {
+// One launch shape: form and tile as the kernels take them, and its blocks.
+struct Launch {
     int variant = 0;
     stn::Tile tile{};
+    int remap = 1;  // XCD-chunked tile order (saturated forms)
+    long long nblocks = 0;
+};
+
+struct BatchClass {
+    int variant = 0;   // as reported
+    stn::Tile tile{};
+    Launch run;        // what its launches are
     int n_items = 0, item_base = 0, grid = 0;
 };
 struct BatchState {
@@ -52,15 +61,17 @@ struct RunGraphs {
 
 struct stencil_plan_s {
     int kind = 0, dtype = 0, bc = 0;
-    int variant = 0;            // resolved form (stn::Variant)
-    stn::Tile tile{};           // resolved launch shape
+    int variant = 0;            // resolved form (stn::Variant), as reported
+    stn::Tile tile{};           // its launch shape, as reported
+    Launch one, many;           // what a run of one sweep, or of more, launches
     stn::Geom g{};
     int rz = 0;                 // z halo width (0 for 2-D)
     double c[5] = {0, 0, 0, 0, 0};
     double omega = 0;
     const stn::KindOps *ops = nullptr;
     int device = -1;
-    long long nblocks = 0;      // blocks of one sweep launch = residual partial count
+    long long nblocks = 0;      // residual partials the plan holds (blocks of its largest launch)
+    long long resid_blocks = 0; // partials the last run left
     double *d_part = nullptr;   // device: per-block residual partials of the last sweep
     double *d_red = nullptr;    // device: first-pass sums of the residual reduction
     int remap = 1;              // XCD-chunked tile order for the saturated forms
@@ -89,8 +100,10 @@ void init_plan_fields(stencil_plan_s *p, const stencil_desc *d, const Geom &g, i
 stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d);
 stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, const void *const *coef_arrays,
                                 SweepArgs &a);
-hipError_t run_pre(stencil_plan_s *p, void *const *fields, hipStream_t s);
-hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int iterations, hipStream_t s,
-                      int *launches, double *part);
+void default_launches(stencil_plan_s *p, int requested);
+const Launch &run_launch(const stencil_plan_s *p, int iterations);
+hipError_t run_pre(stencil_plan_s *p, void *const *fields, const Launch &l, hipStream_t s);
+hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int iterations, const Launch &l,
+                      hipStream_t s, int *launches, double *part);
 hipError_t run_post(stencil_plan_s *p, void *const *fields, int launches, hipStream_t s);
 }  // namespace stn

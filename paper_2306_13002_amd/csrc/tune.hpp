@@ -31,6 +31,10 @@ struct TuneEntry {
     Tile tile;
     int remap;    // 0 natural, 1 XCD-chunked
     double us;    // median time per sweep of the winner
+    // what the plan launches instead where that is faster still with the same
+    // results (HEAT3D7 register tiles); run_variant < 0: nothing
+    int run_variant = -1;
+    Tile run_tile{};
 };
 
 // One launch candidate: form, shape and tile map (remap 1 = XCD-chunked).
@@ -54,6 +58,9 @@ StencilInfo stencil_info(const stencil_desc *d, const Geom &g);
 // Candidates the tuners consider for a plan's kind and geometry, restricted
 // by the request's fixed fields.
 std::vector<Cand> tune_candidates(const KindOps *ops, int kind, const Geom &g, const TuneRequest &rq);
+// Launches the tuners time beside the candidates of a request that leaves the
+// shape open (see TuneEntry::run_variant).
+std::vector<Cand> run_candidates(int kind, const Geom &g, const TuneRequest &rq);
 void cost_features(const StencilInfo &si, const Cand &c, float out[24]);
 stencil_status tune_model(stencil_plan_s *p, const TuneRequest &rq, TuneEntry *best);
 
