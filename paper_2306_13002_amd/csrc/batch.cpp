@@ -3,11 +3,11 @@
 // Problems are grouped into size classes by their largest interior edge
 // (<= 64, then buckets of 32).  Each class gets one form and launch shape
 // (tuned by timing the class's own work list over all its problems, or the
-// defaults) and a work list of (problem, tile) items.  A run is one hipGraph: the halo copies,
-// then per class a chain of T work-list launches (classes are
-// parallel branches of the graph), then the odd-T tail copies.  The graph is
-// captured at the first run with a given (T, field pointers) and replayed
-// afterwards.
+// defaults) and a work list of (problem, tile) items.  A run is one hipGraph
+// of parallel branches, one per class: one launch for the class's halo
+// copies, a chain of work-list launches, and after an odd number of them one
+// launch for the copies back.  The graph is captured at the first run with a
+// given (T, field pointers) and replayed afterwards.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -279,9 +279,6 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
         if (g) (void)hipGraphDestroy(g);
         return hip_fail(err, what);
     };
-    for (int i = 0; i < b->count; ++i)
-        if ((e = launch_halo_copy(fields[2 * i], fields[2 * i + 1], 8, b->probs[i].g, 1, cap)) != hipSuccess)
-            return abort_capture(e, "halo copy");
     const int nc = (int)b->classes.size();
     std::vector<int> launches(nc, 0);  // per class; each launch flips the problems' buffers
     if ((e = hipEventRecord(b->evs[0], cap)) != hipSuccess) return abort_capture(e, "fork");
@@ -289,6 +286,9 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
         const BatchClass &C = b->classes[c];
         hipStream_t s = b->side[c];
         if ((e = hipStreamWaitEvent(s, b->evs[0], 0)) != hipSuccess) return abort_capture(e, "fork wait");
+        const int *members = b->d_members + C.member_base;
+        if ((e = launch_batch_copy(false, b->d_probs, members, C.n_members, C.largest, s)) != hipSuccess)
+            return abort_capture(e, "halo copies");
         // a two-sweep class starts an odd sweep count with one single sweep; a
         // three-sweep class starts with one launch of the remainder's sweeps
         const int cv = C.run.variant, per = sweeps_per_launch(cv), rem = T % per;
@@ -302,13 +302,12 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
             t += adv;
             ++launches[c];
         }
+        if ((launches[c] & 1) &&
+            (e = launch_batch_copy(true, b->d_probs, members, C.n_members, C.largest, s)) != hipSuccess)
+            return abort_capture(e, "tail copies");
         if ((e = hipEventRecord(b->evs[1 + c], s)) != hipSuccess) return abort_capture(e, "join");
         if ((e = hipStreamWaitEvent(cap, b->evs[1 + c], 0)) != hipSuccess) return abort_capture(e, "join wait");
     }
-    for (int i = 0; i < b->count; ++i)
-        if (launches[b->prob_class[i]] & 1)
-            if ((e = launch_interior_copy(fields[2 * i + 1], fields[2 * i], 8, b->probs[i].g, 1, cap)) != hipSuccess)
-                return abort_capture(e, "tail copy");
     if ((e = hipStreamEndCapture(cap, &b->graph)) != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
     if ((e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0)) != hipSuccess)
         return hip_fail(e, "hipGraphInstantiate");
@@ -326,6 +325,7 @@ void free_batch(BatchState *b) {
     if (b->d_items) (void)hipFree(b->d_items);
     if (b->d_probs) (void)hipFree(b->d_probs);
     if (b->d_seg) (void)hipFree(b->d_seg);
+    if (b->d_members) (void)hipFree(b->d_members);
     if (b->d_part) (void)hipFree(b->d_part);
     if (b->d_res) (void)hipFree(b->d_res);
     if (b->h_res) (void)hipHostFree(b->h_res);
@@ -428,6 +428,7 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
         if (r < 0 || v > (long long)geoms[r].nx * geoms[r].ny * geoms[r].nz) rep[cls[i]] = i;
     }
     std::vector<BatchItem> items;
+    std::vector<int> order;  // problems by class
     std::vector<int> seg(2 * count, 0);
     hipError_t e;
     stencil_status st = STENCIL_OK;
@@ -488,6 +489,12 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
             C.run.variant = d.variant == STENCIL_AUTO ? V_SAT3 : C.variant;
             C.run.tile = h3_default_tile(C.run.variant, gs);
         }
+        C.member_base = (int)order.size();
+        C.n_members = (int)members.size();
+        for (int i : members) {
+            order.push_back(i);
+            C.largest = std::max(C.largest, (long long)geoms[i].nx * geoms[i].ny * geoms[i].nz);
+        }
         C.item_base = (int)items.size();
         std::vector<std::pair<int, int>> ranges;
         std::vector<BatchItem> ci = class_items(members, geoms, C.run.tile, &ranges);
@@ -515,6 +522,7 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
     if ((e = hipMalloc(&b->d_items, sizeof(BatchItem) * items.size())) != hipSuccess ||
         (e = hipMalloc(&b->d_probs, sizeof(BatchProb) * count)) != hipSuccess ||
         (e = hipMalloc(&b->d_seg, sizeof(int) * 2 * count)) != hipSuccess ||
+        (e = hipMalloc(&b->d_members, sizeof(int) * count)) != hipSuccess ||
         (e = hipMalloc(&b->d_part, sizeof(double) * items.size())) != hipSuccess ||
         (e = hipMalloc(&b->d_res, sizeof(double) * count)) != hipSuccess ||
         (e = hipHostMalloc(&b->h_res, sizeof(double) * count, hipHostMallocDefault)) != hipSuccess) {
@@ -523,6 +531,7 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
     }
     if ((e = hipMemcpy(b->d_items, items.data(), sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice)) !=
             hipSuccess ||
+        (e = hipMemcpy(b->d_members, order.data(), sizeof(int) * count, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(b->d_seg, seg.data(), sizeof(int) * 2 * count, hipMemcpyHostToDevice)) != hipSuccess) {
         free_plan(p);
         return hip_fail(e, "batch tables upload");

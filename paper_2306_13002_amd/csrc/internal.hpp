@@ -98,6 +98,10 @@ hipError_t launch_halo_copy(const void *src, void *dst, int elem_bytes, const Ge
 hipError_t launch_periodic_fill(void *buf, int elem_bytes, const Geom &g, int rz, hipStream_t s);
 hipError_t launch_fill(void *buf, long long n, int elem_bytes, double value, hipStream_t s);
 hipError_t launch_interior_copy(const void *src, void *dst, int elem_bytes, const Geom &g, int rz, hipStream_t s);
+// The halo copies (f[0] -> f[1]) or the interior copies back (tail: f[1] ->
+// f[0]) of n problems of a batch, members: their indices (device).
+hipError_t launch_batch_copy(bool tail, const BatchProb *probs, const int *members, int n, long long largest,
+                             hipStream_t s);
 // Two fixed-order passes: up to kReduceBlocks blocks each sum a contiguous
 // chunk of part[] into scratch[], then one block sums scratch[].
 constexpr int kReduceBlocks = 256;

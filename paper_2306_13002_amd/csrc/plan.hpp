@@ -24,6 +24,8 @@ struct BatchClass {
     stn::Tile tile{};
     Launch run;        // what its launches are
     int n_items = 0, item_base = 0, grid = 0;
+    int n_members = 0, member_base = 0;  // its problems in BatchState::d_members
+    long long largest = 0;               // interior cells of the largest of them
 };
 struct BatchState {
     int count = 0, n_items = 0;
@@ -32,6 +34,7 @@ struct BatchState {
     std::vector<int> prob_class;        // index into classes, per problem
     stn::BatchItem *d_items = nullptr;  // class-major, then problem, then tile (x fastest)
     stn::BatchProb *d_probs = nullptr;
+    int *d_members = nullptr;           // problem indices, class-major
     int *d_seg = nullptr;               // per problem: item begin [count], item end [count]
     double *d_part = nullptr;           // residual partial per item
     double *d_res = nullptr;            // residual per problem
