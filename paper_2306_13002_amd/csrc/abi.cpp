@@ -302,6 +302,8 @@ stencil_status alloc_plan_buffers(stencil_plan_s *p) {
         l->nblocks = p->ops->nblocks(l->variant, l->tile, p->g);
     }
     p->nblocks = std::max(p->one.nblocks, p->many.nblocks);
+    for (int k = 1; k <= kMarchMax && p->march; ++k)
+        p->nblocks = std::max(p->nblocks, p->ops->nblocks(V_MARCH, h2_march_tile(k, p->g), p->g));
     if ((e = hipMalloc(&p->d_part, sizeof(double) * (size_t)p->nblocks)) != hipSuccess)
         return fail(STENCIL_E_NOMEM, "hipMalloc residual partials (%lld blocks): %s", p->nblocks, hipGetErrorString(e));
     if ((e = hipMalloc(&p->d_red, sizeof(double) * kReduceBlocks)) != hipSuccess)
@@ -364,16 +366,28 @@ struct DeviceGuard {
 //    several per pass (HEAT3D7 three), which read and write the grid once
 //    (400^3, six sweeps: 1690 us single, 535 us by threes; 61 x 48 x 53, ten
 //    sweeps and the residual: 80 us in ten launches, 48 us in four).
+//  - AUTO HEAT2D5 runs of more than one sweep march (heat2d5_march).
 void default_launches(stencil_plan_s *p, int requested) {
     const bool several = requested == STENCIL_AUTO && p->bc == STENCIL_BC_DIRICHLET;
     if (p->kind == STENCIL_HEAT3D7 && p->variant != V_PLAIN) {
         p->one = Launch{p->variant, h3_default_tile(p->variant, {p->g})};
         p->many = several ? Launch{V_SAT3, h3_default_tile(V_SAT3, {p->g})} : p->one;
     }
+    p->march = p->kind == STENCIL_HEAT2D5 && several;
 }
 
-// The launch shape of a run of `iterations` sweeps.
-const Launch &run_launch(const stencil_plan_s *p, int iterations) { return iterations > 1 ? p->many : p->one; }
+// The launch shape of a run of `iterations` sweeps.  Marching HEAT2D5 runs
+// take an even number of launches (the result then ends in fields[0] without
+// a copy back) of at most kMarchMax sweeps, as equal as they can be.
+Launch run_launch(const stencil_plan_s *p, int iterations) {
+    if (iterations <= 1) return p->one;
+    if (!p->march) return p->many;
+    if (iterations == 2) return p->one;  // marching one sweep at a time is slower than the plain kernel
+    const int half = (iterations + 2 * kMarchMax - 1) / (2 * kMarchMax);
+    Launch l{V_MARCH, h2_march_tile((int)cdiv(iterations, 2LL * half), p->g)};
+    l.nblocks = p->ops->nblocks(l.variant, l.tile, p->g);
+    return l;
+}
 
 stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
     const KindOps *ops = p->ops;
@@ -422,7 +436,8 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
         p->tile = e.tile;
         p->remap = e.remap;
         p->tuned = true;
-        if (e.run_variant >= 0) p->one = p->many = Launch{e.run_variant, e.run_tile};
+        if (e.run_variant == V_MARCH) p->march = true;
+        else if (e.run_variant >= 0) p->one = p->many = Launch{e.run_variant, e.run_tile};
         return STENCIL_OK;
     }
     int v = dv;
@@ -489,7 +504,8 @@ stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, co
 // Jacobi kinds first copy the state's halo into the scratch grid.
 hipError_t run_pre(stencil_plan_s *p, void *const *fields, const Launch &l, hipStream_t s) {
     if (p->kind == STENCIL_WAVE25 || p->bc != STENCIL_BC_DIRICHLET) return hipSuccess;
-    // fused HEAT2D5 sweeps write the scratch grid's boundary ring themselves
+    // fused and marching HEAT2D5 sweeps write the scratch grid's boundary ring themselves
+    if (l.variant == V_MARCH) return hipSuccess;
     if (p->kind == STENCIL_HEAT2D5 && launch_sweeps(p->kind, l.variant, l.tile) > 1) return hipSuccess;
     return launch_halo_copy(fields[0], fields[1], elem_bytes(p->dtype), p->g, p->rz, s);
 }
@@ -509,7 +525,7 @@ hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int i
     // three-sweep form three (the first launch takes the remainder of the
     // count)
     const int per = launch_sweeps(p->kind, l.variant, l.tile);
-    const bool fused = (p->kind == STENCIL_HEAT2D5 && per > 1) || l.variant == V_SAT3;
+    const bool fused = (p->kind == STENCIL_HEAT2D5 && per > 1) || l.variant == V_SAT3 || l.variant == V_MARCH;
     hipError_t e;
     *launches = 0;
     for (int t = 0; t < iterations;) {
@@ -552,7 +568,7 @@ hipError_t capture_run(stencil_plan_s *p, void *const *fields, const SweepArgs &
         return e;
     }
     int launches = 0;
-    const Launch &l = run_launch(p, iterations);
+    const Launch l = run_launch(p, iterations);
     for (int part = 0; part < 3 && e == hipSuccess; ++part) {
         if ((e = hipStreamBeginCapture(rg->cap, hipStreamCaptureModeThreadLocal)) != hipSuccess) break;
         const hipError_t le = part == 0 ? run_pre(p, fields, l, rg->cap)
@@ -636,7 +652,7 @@ stencil_status stencil_run(stencil_plan_t p, void *const *fields, const void *co
     if (!guard.ok) return fail(STENCIL_E_DEVICE, "cannot make device %d current", p->device);
     hipStream_t s = (hipStream_t)stream_;
     hipError_t e;
-    const Launch &l = run_launch(p, iterations);
+    const Launch l = run_launch(p, iterations);
     p->has_resid = false;
     p->resid_blocks = l.nblocks;
     std::vector<const void *> sig{fields[0], fields[1]};
@@ -699,7 +715,7 @@ stencil_status stencil_run_noalloc(stencil_plan_t p, void *const *fields, const 
     if (p->kind == STENCIL_GENERIC && p->variant == V_SATURATED && p->base_args.rtc)
         return fail(STENCIL_E_UNSUPPORTED, "generated GENERIC kernels are looked up by their source text at launch; "
                                            "the allocation-free run takes the table-driven kernel only");
-    const Launch &l = run_launch(p, iterations);
+    const Launch l = run_launch(p, iterations);
     if (l.nblocks > kNoallocPartials)
         return fail(STENCIL_E_UNSUPPORTED, "the plan's sweep launch has %lld blocks; the allocation-free run holds at most %lld",
                     l.nblocks, kNoallocPartials);

@@ -191,6 +191,117 @@ __global__ __launch_bounds__(1024) void heat2d5_fused_cell(const double *__restr
     }
 }
 
+__device__ __forceinline__ double lane_prev(double v) {  // lane i <- lane i - 1 (lane 0 <- 0)
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double lane_next(double v) {  // lane i <- lane i + 1 (lane 63 <- 0)
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xF, 0xF, true));
+}
+
+// PLAIN 2-D, KK sweeps per launch, marching: a wave holds a strip of 64
+// columns (64 - 2*rim of them its own, rim >= KK) and walks the rows of its
+// y-block.  At step p row p arrives (loaded five steps earlier) and sweep j
+// runs on row p - j: the rows above and below are the lane's own values, the
+// x neighbours those of the next lanes.  Nothing passes through LDS and no
+// wave waits for another.  The plain body's operands and order: each product
+// cn * u is rounded once, as there, and shared by the four cells that add it.
+// Cells that are not interior keep their value, and the launch writes dst's
+// boundary ring (no halo copy precedes it).  Bit for bit KK single launches.
+//
+// Bound by issuing 12 vector instructions per cell and sweep once the grid is
+// large, by the march's latency when it is small.  us per call of ten sweeps
+// and the residual, one launch per sweep -> two launches of five: 256^2 80 ->
+// 31, 1999 x 1501 140 -> 54.
+template <int KK>
+__global__ __launch_bounds__(256) void heat2d5_march(const double *__restrict__ src, double *__restrict__ dst, Geom g,
+                                                     double cc, double cn, int rim, int yb,
+                                                     double *__restrict__ part) {
+    constexpr int NS = 8, PF = NS - 3;  // row slots: three in use, five in flight
+    __shared__ double red[kMaxWaves];
+    const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int PX = g.nx + 2, PY = g.ny + 2, width = 64 - 2 * rim;
+    const int strip = blockIdx.x * 4 + w;
+    const int X = strip * width + 1 - rim + lane;
+    const int j0 = blockIdx.y * yb + 1, j1 = min(j0 + yb - 1, g.ny);  // own rows (padded coordinates)
+    double acc = 0.0;
+    if (strip * width < g.nx) {
+        const bool inx = X >= 1 && X <= g.nx;
+        const unsigned long long inxm = __ballot(inx);
+        const bool own = lane >= rim && lane < 64 - rim && inx;
+        // ring cells belong to the strip and block whose cell is nearest
+        const bool ownx = own || (X == 0 && lane == rim - 1) || (X == PX - 1 && lane >= rim && lane <= 64 - rim);
+        const int o0 = j0 == 1 ? 0 : j0, o1 = j1 == g.ny ? PY - 1 : j1;  // rows written
+        const unsigned xo = (unsigned)min(max(X, 0), PX - 1) * 8u;
+        const long long pyb = g.py * 8;
+        const int p0 = j0 - KK, pE = o1 + KK;
+        const char *row = (const char *)(src + (long long)max(p0, 0) * g.py);
+        char *out = (char *)dst + (long long)o0 * pyb;
+        double u[KK][NS], q[KK][NS];  // after j sweeps: value and cn * value of the row in slot (row - p0) mod 8
+#pragma unroll
+        for (int j = 0; j < KK; ++j)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) u[j][s] = q[j][s] = 0.0;
+        auto load = [&](const int p, const int s) {  // row p clamped into the array; then advance
+            u[0][s] = buf_ld_f64(plane_rsrc(row), xo);
+            row += p >= 0 && p < PY - 1 ? pyb : 0;
+        };
+#pragma unroll
+        for (int d = 0; d < PF; ++d) load(p0 + d, d);
+        auto step = [&](const int p, const int s) {  // s = (p - p0) mod 8
+            load(p + PF, (s + PF) % NS);
+            q[0][s] = cn * u[0][s];
+#pragma unroll
+            for (int j = 1; j <= KK; ++j) {
+                const int y = p - j, c = (s + 2 * NS - j) % NS, m = (s + 2 * NS - j - 1) % NS, a = (s + 2 * NS - j + 1) % NS;
+                const double o = u[j - 1][c];
+                double v = cc * o;
+                v = v + lane_prev(q[j - 1][c]);
+                v = v + lane_next(q[j - 1][c]);
+                v = v + q[j - 1][m];
+                v = v + q[j - 1][a];
+                // (a select: a branch would serialize the sweeps, of which only
+                // the last addition and this wait for each other)
+                v = __builtin_amdgcn_inverse_ballot_w64(y >= 1 && y <= g.ny ? inxm : 0ull) ? v : o;
+                if (j < KK) {
+                    u[j < KK ? j : 0][c] = v;
+                    q[j < KK ? j : 0][c] = cn * v;
+                } else if (y >= o0) {
+                    if (ownx) buf_st_f64(plane_rsrc(out), xo, v);
+                    if (part && own && y >= j0 && y <= j1) {
+                        const double d = v - o;
+                        acc = acc + d * d;
+                    }
+                    out += pyb;
+                }
+            }
+        };
+        for (int p = p0;; p += NS) {
+            if (p > pE) break;
+            step(p, 0);
+            if (p + 1 > pE) break;
+            step(p + 1, 1);
+            if (p + 2 > pE) break;
+            step(p + 2, 2);
+            if (p + 3 > pE) break;
+            step(p + 3, 3);
+            if (p + 4 > pE) break;
+            step(p + 4, 4);
+            if (p + 5 > pE) break;
+            step(p + 5, 5);
+            if (p + 6 > pE) break;
+            step(p + 6, 6);
+            if (p + 7 > pE) break;
+            step(p + 7, 7);
+        }
+    }
+    if (part) {
+        const double sum = block_sum_f64(acc, red);
+        if (threadIdx.x == 0 && threadIdx.y == 0) part[block_linear_id()] = sum;
+    }
+}
+
 // Plain 3-D body for one block-shaped tile (bx, by, bz) of blockDim points;
 // returns this thread's squared change.
 __device__ __forceinline__ double heat3d7_plain_tile(const double *__restrict__ src, double *__restrict__ dst,
@@ -629,15 +740,6 @@ __global__ __launch_bounds__(RX *RY) void heat3d7_sat3(const double *__restrict_
 // sweeps 160^3 31.4 -> 20.4, 400^3 330 -> 253; one sweep 400^3 280 -> 233.
 // Deeper prefetch (2 or 3 planes), x neighbours through LDS, 8 rows per
 // thread and 4 to 6 sweeps per pass measured no better.
-__device__ __forceinline__ double lane_prev(double v) {  // lane i <- lane i - 1 (lane 0 <- 0)
-    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xF, 0xF, true),
-                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ double lane_next(double v) {  // lane i <- lane i + 1 (lane 63 <- 0)
-    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xF, 0xF, true),
-                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xF, 0xF, true));
-}
-
 template <int H, int KK, int RY, int NW>
 struct H3Rt {
     static_assert(KK >= 1 && KK <= H && H <= 3, "the rim is at least as wide as the sweeps are many");
@@ -892,9 +994,27 @@ bool h2_tile_ok(int v, Tile t) {
            (h2_cell_tile(t) || t.tx == 16 || t.tx == 32);
 }
 
-long long h2_nblocks(int, Tile t, const Geom &g) { return cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty); }
+// V_MARCH tiles: (rim, rows per y-block, 0); a launch performs 1..rim sweeps.
+long long h2_nblocks(int v, Tile t, const Geom &g) {
+    if (v == V_MARCH) return cdiv(cdiv(g.nx, 64 - 2 * t.tx), 4) * cdiv(g.ny, t.ty);
+    return cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty);
+}
 
 hipError_t h2_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
+    if (v == V_MARCH) {
+        if (t.tx < 1 || t.tx > kMarchMax || t.ty < 1 || a.sweeps < 1 || a.sweeps > t.tx) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)cdiv(cdiv(a.g.nx, 64 - 2 * t.tx), 4), (unsigned)cdiv(a.g.ny, t.ty), 1);
+        switch (a.sweeps) {
+#define X(K)                                                                                                        \
+    case K:                                                                                                        \
+        hipLaunchKernelGGL(heat2d5_march<K>, grid, dim3(64, 4, 1), 0, s, (const double *)a.src, (double *)a.dst, a.g, \
+                           a.c[0], a.c[1], t.tx, t.ty, a.part);                                                    \
+        break;
+            X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+#undef X
+        }
+        return hipGetLastError();
+    }
     if (v != V_PLAIN) return hipErrorInvalidValue;
     if (t.tz > 1) {
         if (a.sweeps < 1 || a.sweeps > t.tz) return hipErrorInvalidValue;
@@ -1198,6 +1318,29 @@ Tile h3_default_tile(int v, const std::vector<Geom> &gs) {
             }
         }
     }
+    return best;
+}
+
+// The marching launch of a run in passes of up to k sweeps: rows per block
+// with the lowest estimate of (rows + 2k) * (54 k + 60) cycles * (waves per
+// SIMD + 0.7).  Measured us for two launches of k = 5 (8), rows 4 / 8 / 16 /
+// 32 / 64, the pick in brackets: 256^2 [14.0] / 15.7 / 19.3 / 26.8 / 42
+// ([19.4] / 21.6 / 26.5 / 36 / 56); 1999 x 1501 57.6 / 45.5 / [40.1] / 40.0 /
+// 48.2 (127 / 86 / [69] / 69 / 63); 3000^2 136 / 99 / 82 / [80] / 80 (335 /
+// 218 / 158 / 127 / [113]).
+Tile h2_march_tile(int k, const Geom &g) {
+    Tile best{k, 4, 0};
+    double cost = 0;
+    for (int yb : {4, 8, 16, 32, 64, 128}) {
+        if (yb > 4 && yb >= 2 * g.ny) break;
+        const double waves = (double)cdiv(cdiv(g.nx, 64 - 2 * k), 4) * 4 * cdiv(g.ny, yb);
+        const double est = (yb + 2 * k) * (54.0 * k + 60) * (std::max(1.0, waves / 1024) + 0.7);
+        if (cost == 0 || est < cost) {
+            cost = est;
+            best.ty = yb;
+        }
+    }
+    while (h2_nblocks(V_MARCH, best, g) > kNoallocPartials) best.ty *= 2;
     return best;
 }
 

@@ -13,7 +13,8 @@ namespace stn {
 // the paper's ablation (rewritten arithmetic only, bulk load only, both);
 // V_SAT2 is the saturated form with two sweeps per pass (POISSON19, HEAT3D7),
 // V_SAT3 with three (HEAT3D7).
-enum Variant { V_PLAIN = 0, V_SATURATED = 1, V_CSE_SAT = 3, V_CSE_BULK = 4, V_ACCSAT_POINT = 5, V_SAT2 = 6, V_SAT3 = 7 };
+enum Variant { V_PLAIN = 0, V_SATURATED = 1, V_CSE_SAT = 3, V_CSE_BULK = 4, V_ACCSAT_POINT = 5, V_SAT2 = 6, V_SAT3 = 7,
+               V_MARCH = 8 };
 inline bool is_point_form(int v) { return v == V_CSE_SAT || v == V_CSE_BULK || v == V_ACCSAT_POINT; }
 // Sweeps one full launch performs (a V_SAT3 launch may be asked for fewer).
 inline int sweeps_per_launch(int v) { return v == V_SAT2 ? 2 : (v == V_SAT3 ? 3 : 1); }
@@ -88,6 +89,9 @@ struct KindOps {
 // HEAT3D7: default tile of a saturated form over one grid, or over the grids
 // of a batch class.
 Tile h3_default_tile(int variant, const std::vector<Geom> &gs);
+// HEAT2D5: marching launches, up to kMarchMax sweeps each.
+constexpr int kMarchMax = 8;
+Tile h2_march_tile(int k, const Geom &g);
 // The register tiles of a saturated form (at most 8; tz = 0).
 int h3_rt_tiles(int variant, Tile *out);
 

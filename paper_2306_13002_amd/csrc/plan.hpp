@@ -67,6 +67,7 @@ struct stencil_plan_s {
     int variant = 0;            // resolved form (stn::Variant), as reported
     stn::Tile tile{};           // its launch shape, as reported
     Launch one, many;           // what a run of one sweep, or of more, launches
+    bool march = false;         // HEAT2D5: runs of more sweeps march (see run_launch)
     stn::Geom g{};
     int rz = 0;                 // z halo width (0 for 2-D)
     double c[5] = {0, 0, 0, 0, 0};
@@ -104,7 +105,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d);
 stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, const void *const *coef_arrays,
                                 SweepArgs &a);
 void default_launches(stencil_plan_s *p, int requested);
-const Launch &run_launch(const stencil_plan_s *p, int iterations);
+Launch run_launch(const stencil_plan_s *p, int iterations);
 hipError_t run_pre(stencil_plan_s *p, void *const *fields, const Launch &l, hipStream_t s);
 hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int iterations, const Launch &l,
                       hipStream_t s, int *launches, double *part);

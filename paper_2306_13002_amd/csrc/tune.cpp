@@ -168,7 +168,10 @@ std::vector<Cand> tune_candidates(const KindOps *ops, int kind, const Geom &g, c
 
 std::vector<Cand> run_candidates(int kind, const Geom &g, const TuneRequest &rq) {
     std::vector<Cand> out;
-    if (kind != STENCIL_HEAT3D7 || rq.tile_x || rq.tile_y || rq.zblock) return out;
+    if (rq.tile_x || rq.tile_y || rq.zblock) return out;
+    if (kind == STENCIL_HEAT2D5 && rq.bc == STENCIL_BC_DIRICHLET)
+        for (int k : {4, 5, 8}) out.push_back({V_MARCH, h2_march_tile(k, g), 0});
+    if (kind != STENCIL_HEAT3D7) return out;
     for (int v : {(int)V_SATURATED, (int)V_SAT2, (int)V_SAT3}) {
         if (rq.variant != STENCIL_AUTO && rq.variant != v) continue;
         if (v != V_SATURATED && rq.bc != STENCIL_BC_DIRICHLET) continue;

@@ -22,6 +22,7 @@ struct TuneRequest {
 // Sweeps one launch of (kind, variant, tile) performs: the two-sweep form
 // does two; HEAT2D5 PLAIN with tile.tz > 1 fuses tile.tz sweeps per launch.
 inline int launch_sweeps(int kind, int variant, const Tile &t) {
+    if (variant == V_MARCH) return t.tx;
     if (kind == STENCIL_HEAT2D5 && variant == V_PLAIN && t.tz > 1) return t.tz;
     return sweeps_per_launch(variant);
 }
