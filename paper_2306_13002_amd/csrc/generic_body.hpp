@@ -59,10 +59,10 @@ struct Phase {
     static constexpr int value = N;
 };
 
-template <typename T, int R, int TX, int BY, int RY, bool CORNERS, typename OFF, class Slots>
+template <typename T, int R, int TX, int BY, int RY, bool CORNERS, typename OFF, class Slots, typename L>
 __device__ __forceinline__ double generic_rows_body(const T *__restrict__ src, T *__restrict__ dst, const Geom &g,
                                                     int zb, int bx, int by, int bz, bool want_res, const Slots &slots,
-                                                    double (*tile)[(BY * RY + 2 * R) * (TX + 2 * R)]) {
+                                                    L (*tile)[(BY * RY + 2 * R) * (TX + 2 * R)]) {
     constexpr int TY = BY * RY, W = TX + 2 * R, NT = TX * BY, NQ = 2 * R + 1;
     constexpr int BW = CORNERS ? W : TX, X0 = CORNERS ? 0 : R;
     constexpr int NH = 2 * R * BW + 2 * R * TY, HR = (NH + NT - 1) / NT;
@@ -122,11 +122,11 @@ __device__ __forceinline__ double generic_rows_body(const T *__restrict__ src, T
     auto step = [&](auto phase) -> bool {
         constexpr int PH = decltype(phase)::value, LAST = (2 * R - PH + NQ) % NQ;
         if (zp > zend) return false;
-        double *t = tile[b];
+        L *t = tile[b];
 #pragma unroll
-        for (int m = 0; m < RY; ++m) t[me + m * W] = (double)cv[m];
+        for (int m = 0; m < RY; ++m) t[me + m * W] = (L)cv[m];
 #pragma unroll
-        for (int s = 0; s < HR; ++s) t[hl[s]] = (double)hv[s];
+        for (int s = 0; s < HR; ++s) t[hl[s]] = (L)hv[s];
         if (zp < zend) pl += pzb;
         load();  // the next plane (the last one again at the end)
         __syncthreads();

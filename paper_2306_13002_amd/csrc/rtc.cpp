@@ -56,7 +56,7 @@ struct SlotEmitter {
     const int RY, W, phase;  // phase: see generic_rows_body
     std::string o;
     std::map<std::string, std::string> memo;  // expression -> name
-    int n_add = 0, n_fma = 0, n_name = 0;
+    int n_add = 0, n_fma = 0, n_cell = 0, n_name = 0;
 
     SlotEmitter(const RtcSpec &sp_, int ry, int w, int ph) : sp(sp_), RY(ry), W(w), phase(ph) {}
 
@@ -73,7 +73,11 @@ struct SlotEmitter {
         return named(expr);
     }
     // cell dx of window row wy (row m of the thread is window row m + R)
-    std::string cell(int dx, int wy) { return named("t[me + " + std::to_string((wy - sp.R) * W + dx) + "]"); }
+    std::string cell(int dx, int wy) {
+        const std::string expr = "t[me + " + std::to_string((wy - sp.R) * W + dx) + "]";
+        if (!memo.count(expr)) ++n_cell;
+        return named(expr);
+    }
     std::string tree(const std::vector<std::string> &v, size_t a, size_t b) {
         if (b - a == 1) return v[a];
         const size_t m = a + (b - a + 1) / 2;
@@ -189,6 +193,7 @@ struct EmitPlan {
     int per_plane;  // FP64 instructions per thread and plane
     bool rotate;    // the accumulator queue moves on by name
     bool guarded;   // slots that are not live are skipped
+    bool narrow;    // F32 storage: the LDS tile holds F32, widened at each read
 };
 
 // What a kernel's source depends on besides its tile, as text.
@@ -252,6 +257,11 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
     // coefficients: 81 -> 64 us a sweep at 201 x 233 x 160); the branches cost
     // small stencils more (star r = 1 at 64^3: 8.4 -> 10.4 us).
     p.guarded = p.per_plane >= 64 * ry;
+    // Widening F32 cells once, as they are staged, doubles the LDS bytes of
+    // every read: worth it unless the stencil does little arithmetic per cell
+    // (star r = 4 321 x 190 x 257: F32 in LDS 56.0 us a sweep, FP64 58.1; box r
+    // = 2 201 x 233 x 160: 61.6 against 57.4).
+    p.narrow = sp.eb == 4 && p.per_plane < 4 * er.n_cell;
     std::lock_guard<std::mutex> lk(g_mu);
     g_specs[key].emit.push_back(p);
     return p;
@@ -301,9 +311,9 @@ std::string rtc_generic_source(RtcSpec &sp, int TX, int TY) {
     o += "#include \"generic_body.hpp\"\n\nnamespace {\nstruct GenSlots {\n    static constexpr bool rotate = ";
     o += ep.rotate ? "true;\n" : "false;\n";
     std::snprintf(buf, sizeof buf,
-                  "    template <int PH>\n    __device__ __forceinline__ void add(const double *__restrict__ t, int me, "
+                  "    template <int PH>\n    __device__ __forceinline__ void add(const %s *__restrict__ t, int me, "
                   "unsigned live, double (*acc)[%d]) const {\n",
-                  gr.ry);
+                  ep.narrow ? "float" : "double", gr.ry);
     o += buf;
     for (int ph = 0; ph < (ep.rotate ? 2 * R + 1 : 1); ++ph) {
         SlotEmitter em(sp, gr.ry, W, ph);
@@ -320,8 +330,8 @@ std::string rtc_generic_source(RtcSpec &sp, int TX, int TY) {
                   "%s *__restrict__ dst, stn::Geom g, int zb, int remap, double *__restrict__ part) {\n",
                   TX * gr.by, T, T);
     o += buf;
-    std::snprintf(buf, sizeof buf, "    __shared__ double tile[2][%d];\n    __shared__ double red[16];\n",
-                  (TY + 2 * R) * W);
+    std::snprintf(buf, sizeof buf, "    __shared__ %s tile[2][%d];\n    __shared__ double red[16];\n",
+                  ep.narrow ? "float" : "double", (TY + 2 * R) * W);
     o += buf;
     o += "    int bx, by, bz;\n    stn::tile_coords(remap, bx, by, bz);\n";
     std::snprintf(buf, sizeof buf,
