@@ -358,15 +358,18 @@ struct DeviceGuard {
     }
 };
 
-// Launch shapes of a FIXED or MODEL plan whose descriptor leaves the tile open (the
+// Launch shapes of a FIXED (HEAT3D7 also MODEL) plan whose descriptor leaves the tile open (the
 // plan reports its form's default shape).  Results are those of that form bit
 // for bit; the residual is the same sum taken in another order.
 //  - HEAT3D7 saturated forms run their register tiles (h3_default_tile).
 //  - AUTO lets the plan choose the form: runs of more than one sweep advance
 //    several per pass (HEAT3D7 three), which read and write the grid once
-//    (400^3, six sweeps: 1690 us single, 535 us by threes; 61 x 48 x 53, ten
+//    (400^3, six sweeps: 1690 us single, 558 us by threes; 61 x 48 x 53, ten
 //    sweeps and the residual: 80 us in ten launches, 48 us in four).
 //  - AUTO HEAT2D5 runs of more than one sweep march (heat2d5_march).
+//  - POISSON19 saturated forms size their z-blocks (p19_default_tile); AUTO
+//    runs of more than one sweep make two per pass (255^3 202 -> 128 us a
+//    sweep).
 void default_launches(stencil_plan_s *p, int requested) {
     const bool several = requested == STENCIL_AUTO && p->bc == STENCIL_BC_DIRICHLET;
     if (p->kind == STENCIL_HEAT3D7 && p->variant != V_PLAIN) {
@@ -374,6 +377,10 @@ void default_launches(stencil_plan_s *p, int requested) {
         p->many = several ? Launch{V_SAT3, h3_default_tile(V_SAT3, {p->g})} : p->one;
     }
     p->march = p->kind == STENCIL_HEAT2D5 && several;
+    if (p->kind == STENCIL_POISSON19 && (p->variant == V_SATURATED || p->variant == V_SAT2)) {
+        p->one = Launch{p->variant, p19_default_tile(p->variant, p->g)};
+        p->many = several ? Launch{V_SAT2, p19_default_tile(V_SAT2, p->g)} : p->one;
+    }
 }
 
 // The launch shape of a run of `iterations` sweeps.  Marching HEAT2D5 runs
@@ -417,7 +424,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
             p->tile = e.tile;
             p->remap = e.remap;
             p->tuned = true;
-            if (!d->tile_x && !d->tile_y && !d->zblock) default_launches(p, e.variant);
+            if (p->kind == STENCIL_HEAT3D7 && !d->tile_x && !d->tile_y && !d->zblock) default_launches(p, e.variant);
             return STENCIL_OK;
         }
         if (st != STENCIL_E_STATE) return st;

@@ -89,6 +89,8 @@ struct KindOps {
 // HEAT3D7: default tile of a saturated form over one grid, or over the grids
 // of a batch class.
 Tile h3_default_tile(int variant, const std::vector<Geom> &gs);
+// POISSON19: default tile of a saturated form (V_SATURATED, V_SAT2).
+Tile p19_default_tile(int variant, const Geom &g);
 // HEAT2D5: marching launches, up to kMarchMax sweeps each.
 constexpr int kMarchMax = 8;
 Tile h2_march_tile(int k, const Geom &g);

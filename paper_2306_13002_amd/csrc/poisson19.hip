@@ -27,6 +27,8 @@
 // LDS ring (one barrier per plane), and every global load of the next plane
 // -- its p tile and the 12 coefficients -- is issued before the current
 // plane is computed ("bulk load"), so each wave keeps ~13 loads in flight.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace stn {
@@ -701,6 +703,40 @@ hipError_t p19_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
 }
 
 }  // namespace
+
+// Default tile of a saturated form: the tile and z-block with the lowest
+// estimate of
+//   rounds * (planes + 2 per sweep) * (waves per SIMD + 0.5),
+// the blocks of a round being those a CU holds together (16 waves of the
+// single-sweep kernel, 12 of the two-sweep one).  Measured us per sweep, the
+// pick (the shape before: z-blocks of 32): two sweeps per pass 31^3 32x4x2 3.5
+// (64x8x31 17.2), 64x60x70 64x8x4 5.6 (18.4), 100x90x110 64x8x16 11.9 (19.5),
+// 255x200x100 64x8x16 43.1 (50.6), 127x127x255 64x8x32 22.1; one sweep 31^3
+// 32x8x2 4.0 (128x4x31 20.8), 64x60x70 32x8x2 5.4 (21.8), 255x200x100
+// 128x4x16 51.3 (60.9).
+Tile p19_default_tile(int v, const Geom &g) {
+    struct Shape {
+        int tx, ty, waves;
+    };
+    static const Shape one[] = {{128, 4, 8}, {64, 8, 8}, {32, 8, 4}}, two[] = {{64, 8, 11}, {32, 4, 4}};
+    static_assert(Sat2Shape<64, 8>::NT == 11 * 64 && Sat2Shape<32, 4>::NT == 4 * 64, "waves per block");
+    const bool s2 = v == V_SAT2;
+    Tile best{0, 0, 0};
+    double cost = 0;
+    for (const Shape *sh = s2 ? two : one; sh != (s2 ? two + 2 : one + 3); ++sh)
+        for (int zb : {32, 16, 8, 4, 2}) {
+            const double per_cu = (double)cdiv(cdiv(g.nx, sh->tx) * cdiv(g.ny, sh->ty) * cdiv(g.nz, zb), 256);
+            const double res = std::min(per_cu, (double)((s2 ? 12 : 16) / sh->waves));
+            const double est = per_cu / res * (std::min(zb, g.nz) + (s2 ? 4 : 2)) * (res * sh->waves / 4 + 0.5);
+            if (cost == 0 || est < cost) {
+                cost = est;
+                best = Tile{sh->tx, sh->ty, std::min(zb, g.nz)};
+            }
+        }
+    // the allocation-free run holds 2^17 partials
+    while (p19_nblocks(v, best, g) > kNoallocPartials && best.tz < g.nz) best.tz *= 2;
+    return best;
+}
 
 KindOps poisson19_ops = {p19_tile_ok, p19_sat_tiles, p19_sat2_tiles, p19_nblocks, p19_launch, nullptr};
 
