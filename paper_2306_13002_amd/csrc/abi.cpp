@@ -370,7 +370,8 @@ struct DeviceGuard {
 //  - POISSON19 saturated forms size their z-blocks (p19_default_tile); AUTO
 //    runs of more than one sweep make two per pass (255^3 202 -> 128 us a
 //    sweep).
-void default_launches(stencil_plan_s *p, int requested) {
+//  - WAVE25 sizes tile and z-block by the grid (w25_default_tile).
+void default_launches(stencil_plan_s *p, const stencil_desc *d, int requested) {
     const bool several = requested == STENCIL_AUTO && p->bc == STENCIL_BC_DIRICHLET;
     if (p->kind == STENCIL_HEAT3D7 && p->variant != V_PLAIN) {
         p->one = Launch{p->variant, h3_default_tile(p->variant, {p->g})};
@@ -381,6 +382,9 @@ void default_launches(stencil_plan_s *p, int requested) {
         p->one = Launch{p->variant, p19_default_tile(p->variant, p->g)};
         p->many = several ? Launch{V_SAT2, p19_default_tile(V_SAT2, p->g)} : p->one;
     }
+    if (p->kind == STENCIL_WAVE25 && p->variant == V_SATURATED)
+        p->one = p->many = Launch{V_SATURATED, w25_default_tile(p->g)};
+    if (d->tile_map) p->one.remap = p->many.remap = p->remap;  // the caller's tile order
 }
 
 // The launch shape of a run of `iterations` sweeps.  Marching HEAT2D5 runs
@@ -424,7 +428,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
             p->tile = e.tile;
             p->remap = e.remap;
             p->tuned = true;
-            if (p->kind == STENCIL_HEAT3D7 && !d->tile_x && !d->tile_y && !d->zblock) default_launches(p, e.variant);
+            if (p->kind == STENCIL_HEAT3D7 && !d->tile_x && !d->tile_y && !d->zblock) default_launches(p, d, e.variant);
             return STENCIL_OK;
         }
         if (st != STENCIL_E_STATE) return st;
@@ -444,7 +448,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
         p->remap = e.remap;
         p->tuned = true;
         if (e.run_variant == V_MARCH) p->march = true;
-        else if (e.run_variant >= 0) p->one = p->many = Launch{e.run_variant, e.run_tile};
+        else if (e.run_variant >= 0) p->one = p->many = Launch{e.run_variant, e.run_tile, d->tile_map ? p->remap : 1};
         return STENCIL_OK;
     }
     int v = dv;
@@ -464,7 +468,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
     p->variant = v;
     p->tile = t;
     p->remap = d->tile_map ? (d->tile_map == 2) : default_remap(p->kind);
-    if (!d->tile_x && !d->tile_y && !d->zblock) default_launches(p, dv);
+    if (!d->tile_x && !d->tile_y && !d->zblock) default_launches(p, d, dv);
     return STENCIL_OK;
 }
 

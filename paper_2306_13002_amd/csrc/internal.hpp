@@ -91,6 +91,8 @@ struct KindOps {
 Tile h3_default_tile(int variant, const std::vector<Geom> &gs);
 // POISSON19: default tile of a saturated form (V_SATURATED, V_SAT2).
 Tile p19_default_tile(int variant, const Geom &g);
+// WAVE25: default tile of the saturated form.
+Tile w25_default_tile(const Geom &g);
 // HEAT2D5: marching launches, up to kMarchMax sweeps each.
 constexpr int kMarchMax = 8;
 Tile h2_march_tile(int k, const Geom &g);
