@@ -269,37 +269,41 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
 
 }  // namespace
 
-// Default tile of a generated kernel.  32 lanes along x where they leave at
-// least 7 % fewer lanes outside the grid than 64 do, 16 rows, and the z-block
-// with the lowest estimate of
-//   [live planes * 4.7 FP64 + planes * 600] * (waves per SIMD + 0.7)  cycles:
-// 4.7 cycles per FP64 instruction as measured, 600 for staging a plane and
-// its LDS reads, 0.7 for what a block's barriers leave idle.  Small z-blocks
-// give more waves, large ones fewer planes that are loaded only for their
-// neighbours.  Measured us per sweep at z-blocks 4 / 8 / 16 / 32, the pick in
-// brackets: box r = 3 f64 symmetric 256^3 172 / 133 / 117 / [106]; box r = 2
-// f32 201 x 233 x 160 58 / [61] / 73 / 109; star r = 4 f32 321 x 190 x 257
-// 97 / 69 / [59] / 61; box r = 3 f64 128 x 130 x 140 [59] / 75 / 97 / 179.
-// With 64 x 4 tiles, one row per thread and z-blocks of 16 (the default
-// before) these took 163, 93, 94 and 89.
+// Default tile of a generated kernel: the tile and z-block with the lowest
+// estimate, in cycles, of
+//   [live planes * 7 FP64 + planes * (150 + 250 cells staged per thread)
+//    + 60 outputs per thread] * (waves per SIMD + 0.7).
+// The constants are the best fit to 64 random stencils and grids (edges
+// 65..321) at six tiles and six z-blocks each: the pick is within 2.6 % of the
+// best of those in the geometric mean (within 15 % in the worst case); 32 or
+// 64 x 16 tiles alone, with the z-block from a simpler estimate, were 8 % off
+// (37 %).  Small z-blocks and tiles give more waves, large ones fewer
+// planes and rings that are loaded only for their neighbours.  Measured us per
+// sweep at that rule -> now: star r = 4 f64 118 x 86 x 177 22.7 -> 15.8, f32
+// 134 x 267 x 73 25.4 -> 19.6; box r = 3 symmetric f64 127 x 164 x 252 53.0 ->
+// 45.4; box r = 3 f64 65 x 101 x 177 53.9 -> 44.0.
 Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
-    Tile t{64, 16, 4};
-    if (100 * cdiv(g.nx, 32) * 32 <= 93 * cdiv(g.nx, 64) * 64) t.tx = 32;
-    const GenRows gr = gen_rows(t.tx, t.ty);
-    const EmitPlan ep = emit_plan(sp, gr.ry);
-    const double waves = t.tx * gr.by / 64.0, fp = 4.7 * ep.per_plane;
-    double best = 0;
-    for (int zb : {2, 4, 8, 16, 32, 64}) {
-        if (zb > 2 && zb >= 2 * g.nz) break;
-        const double per_cu = (double)cdiv(cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, zb), 256);
-        const double planes = zb + 2 * sp.R, live = ep.guarded && !ep.share ? zb : planes;
-        const double est = (live * fp + planes * 600) * (per_cu * waves / 4 + 0.7);
-        if (zb == 2 || est < best) {
-            best = est;
-            t.tz = zb;
+    static const Tile tiles[] = {{64, 16, 0}, {32, 32, 0}, {32, 16, 0}, {32, 8, 0}, {64, 4, 0}, {32, 4, 0}};
+    Tile best{0, 0, 0};
+    double cost = 0;
+    for (Tile t : tiles) {
+        const GenRows gr = gen_rows(t.tx, t.ty);
+        const EmitPlan ep = emit_plan(sp, gr.ry);
+        const double waves = t.tx * gr.by / 64.0;
+        const double staged = (double)(t.tx + 2 * sp.R) * (t.ty + 2 * sp.R) / (t.tx * gr.by);
+        for (int zb : {2, 4, 8, 16, 32, 64}) {
+            if (zb > 2 && zb >= 2 * g.nz) break;
+            const double per_cu = (double)cdiv(cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, zb), 256);
+            const double out = std::min(zb, g.nz), planes = out + 2 * sp.R, live = ep.guarded && !ep.share ? out : planes;
+            const double block = live * 7 * ep.per_plane + planes * (150 + 250 * staged) + out * gr.ry * 60;
+            const double est = block * (per_cu * waves / 4 + 0.7);
+            if (cost == 0 || est < cost) {
+                cost = est;
+                best = Tile{t.tx, t.ty, zb};
+            }
         }
     }
-    return t;
+    return best;
 }
 
 std::string rtc_generic_source(RtcSpec &sp, int TX, int TY) {
