@@ -273,17 +273,21 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
 // estimate, in cycles, of
 //   [live planes * 7 FP64 + planes * (150 + 250 cells staged per thread)
 //    + 60 outputs per thread] * (waves per SIMD + 0.7).
-// The constants are the best fit to 64 random stencils and grids (edges
-// 65..321) at six tiles and six z-blocks each: the pick is within 2.6 % of the
-// best of those in the geometric mean (within 15 % in the worst case); 32 or
-// 64 x 16 tiles alone, with the z-block from a simpler estimate, were 8 % off
-// (37 %).  Small z-blocks and tiles give more waves, large ones fewer
+// The constants are a fit to 109 random stencils and grids (edges 65..321) at
+// six tiles and six z-blocks each: the pick is within 3.1 % of the best of
+// those in the geometric mean (within 28 % in the worst case); 32 or 64 x 16
+// tiles alone, with the z-block from a simpler estimate, were 7 % off (45 %).
+// Where the two grids exceed the L2s (8 x 4 MB), a stencil of little
+// arithmetic takes no z-block shorter than its halo: the planes that blocks
+// load again then come from memory (star r = 3 f64 288 x 92 x 148 after other
+// work: a call of one sweep 60.9 us with z-blocks of 4, 55.3 with 8).  Small z-blocks and tiles give more waves, large ones fewer
 // planes and rings that are loaded only for their neighbours.  Measured us per
 // sweep at that rule -> now: star r = 4 f64 118 x 86 x 177 22.7 -> 15.8, f32
 // 134 x 267 x 73 25.4 -> 19.6; box r = 3 symmetric f64 127 x 164 x 252 53.0 ->
 // 45.4; box r = 3 f64 65 x 101 x 177 53.9 -> 44.0.
 Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
     static const Tile tiles[] = {{64, 16, 0}, {32, 32, 0}, {32, 16, 0}, {32, 8, 0}, {64, 4, 0}, {32, 4, 0}};
+    const bool beyond_l2 = 2.0 * g.nx * g.ny * g.nz * sp.eb > (32 << 20);
     Tile best{0, 0, 0};
     double cost = 0;
     for (Tile t : tiles) {
@@ -293,6 +297,7 @@ Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
         const double staged = (double)(t.tx + 2 * sp.R) * (t.ty + 2 * sp.R) / (t.tx * gr.by);
         for (int zb : {2, 4, 8, 16, 32, 64}) {
             if (zb > 2 && zb >= 2 * g.nz) break;
+            if (zb < 2 * sp.R && !ep.guarded && beyond_l2 && zb < g.nz) continue;
             const double per_cu = (double)cdiv(cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, zb), 256);
             const double out = std::min(zb, g.nz), planes = out + 2 * sp.R, live = ep.guarded && !ep.share ? out : planes;
             const double block = live * 7 * ep.per_plane + planes * (150 + 250 * staged) + out * gr.ry * 60;
