@@ -296,10 +296,13 @@ long long span_elems(const stencil_plan_s *p) {
 
 stencil_status alloc_plan_buffers(stencil_plan_s *p) {
     hipError_t e;
-    // launches as reported unless the plan's defaults run others
+    // launches as reported unless the plan's defaults run others; flat or thin
+    // grids whose partials only the reported shape keeps within the
+    // allocation-free run's scratch take that one
+    const Launch own{p->variant, p->tile, p->remap, p->ops->nblocks(p->variant, p->tile, p->g)};
     for (Launch *l : {&p->one, &p->many}) {
-        if (l->tile.tx == 0) *l = Launch{p->variant, p->tile, p->remap};
-        l->nblocks = p->ops->nblocks(l->variant, l->tile, p->g);
+        if (l->tile.tx != 0) l->nblocks = p->ops->nblocks(l->variant, l->tile, p->g);
+        if (l->tile.tx == 0 || (l->nblocks > kNoallocPartials && own.nblocks <= kNoallocPartials)) *l = own;
     }
     p->nblocks = std::max(p->one.nblocks, p->many.nblocks);
     for (int k = 1; k <= kMarchMax && p->march; ++k)
