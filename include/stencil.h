@@ -112,7 +112,8 @@ typedef enum { STENCIL_F32 = 1, STENCIL_F64 = 2 } stencil_dtype; /* storage type
  * the plan choose between them and, where a kind offers them, the multi-sweep
  * saturated forms below (FIXED tuning: SATURATED; a HEAT3D7 plan made so, with
  * Dirichlet boundaries and the tile left open, advances runs of several sweeps
- * three per pass, and a HEAT2D5 plan up to eight, bit for bit the same).  The per-point ablation forms of the paper's
+ * three per pass, a POISSON19 plan two, and a HEAT2D5 plan up to eight, bit
+ * for bit the same).  The per-point ablation forms of the paper's
  * evaluation (Sec. Evaluation: CSE, CSE+SAT, CSE+BULK, ACCSAT) exist for WAVE25
  * and POISSON19, one thread per point with every operand from memory (CSE is
  * PLAIN: no address is loaded twice in these bodies):
@@ -275,9 +276,10 @@ stencil_status stencil_residuals(stencil_plan_t p, double *host_out, int32_t cou
  * tile_map is reported as 1 (natural) or 2 (XCD-chunked).  A plan whose tile
  * was left open reports its form with the form's default or tuned shape;
  * HEAT3D7 plans may launch register tiles instead (tile_x, tile_y = 62 x 14,
- * 60 x 28, 58 x 26 and others) and HEAT2D5 plans several sweeps per launch,
- * which give the same grids bit for bit.  A plan
- * asked for a tile launches that tile. */
+ * 60 x 28, 58 x 26 and others), HEAT2D5 plans several sweeps per launch,
+ * and FIXED POISSON19 and WAVE25 plans a tile and z-block that suit the grid,
+ * all of which give the same grids bit for bit.  A plan asked for a tile
+ * launches that tile. */
 stencil_status stencil_plan_config(stencil_plan_t p, int32_t *variant, int32_t *tile_x, int32_t *tile_y,
                                    int32_t *zblock, int32_t *tile_map);
 
