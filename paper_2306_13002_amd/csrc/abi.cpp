@@ -367,8 +367,8 @@ struct DeviceGuard {
 //  - HEAT3D7 saturated forms run their register tiles (h3_default_tile).
 //  - AUTO lets the plan choose the form: runs of more than one sweep advance
 //    several per pass (HEAT3D7 three), which read and write the grid once
-//    (400^3, six sweeps: 1690 us single, 558 us by threes; 61 x 48 x 53, ten
-//    sweeps and the residual: 80 us in ten launches, 48 us in four).
+//    (400^3, six sweeps: 1690 us single, 530 us by threes; 61 x 48 x 53, ten
+//    sweeps and the residual: 80 us in ten launches, 47 us in four).
 //  - AUTO HEAT2D5 runs of more than one sweep march (heat2d5_march).
 //  - POISSON19 saturated forms size their z-blocks (p19_default_tile); AUTO
 //    runs of more than one sweep make two per pass (255^3 202 -> 128 us a
@@ -516,10 +516,17 @@ stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, co
 
 // The three parts of a run on stream s (enqueued eagerly or under capture).
 // Jacobi kinds first copy the state's halo into the scratch grid.
+// Whether a run's first launch stores the scratch grid's halo itself, so that
+// no halo copy goes before it (us per call: 61 x 48 x 53 ten sweeps 49.2 ->
+// 46.6, 160^3 fifty 354 -> 349, 400^3 six 556 -> 530).
+bool first_fills(const stencil_plan_s *p, const Launch &l) {
+    return p->kind == STENCIL_HEAT3D7 && p->bc == STENCIL_BC_DIRICHLET && h3_fills(l.variant, l.tile);
+}
+
 hipError_t run_pre(stencil_plan_s *p, void *const *fields, const Launch &l, hipStream_t s) {
     if (p->kind == STENCIL_WAVE25 || p->bc != STENCIL_BC_DIRICHLET) return hipSuccess;
     // fused and marching HEAT2D5 sweeps write the scratch grid's boundary ring themselves
-    if (l.variant == V_MARCH) return hipSuccess;
+    if (l.variant == V_MARCH || first_fills(p, l)) return hipSuccess;
     if (p->kind == STENCIL_HEAT2D5 && launch_sweeps(p->kind, l.variant, l.tile) > 1) return hipSuccess;
     return launch_halo_copy(fields[0], fields[1], elem_bytes(p->dtype), p->g, p->rz, s);
 }
@@ -550,6 +557,7 @@ hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int i
         const int adv = fused ? (t == 0 && first ? first : per) : sweeps_per_launch(v);
         a.sweeps = adv;
         a.remap = l.remap;
+        a.fill = t == 0 && first_fills(p, l);
         a.src = src;
         a.dst = dst;
         a.part = (t + adv == iterations) ? part : nullptr;

@@ -748,7 +748,9 @@ struct H3Rt {
     typedef double Edge[KK][2][NW][2][64];
 };
 
-template <int H, int KK, int RY, int NW>
+// FILL: the launch also stores the fixed halo around its outputs (the cells' own
+// values), so that a run needs no halo copy before its first sweep.
+template <int H, int KK, int RY, int NW, bool FILL = false>
 __device__ __forceinline__ double heat3d7_rt_tile(const double *__restrict__ src, double *__restrict__ dst,
                                                   const Geom &g, double cc, double cn, int zb, int bx, int by, int bz,
                                                   bool want_res, typename H3Rt<H, KK, RY, NW>::Edge &ex) {
@@ -759,7 +761,9 @@ __device__ __forceinline__ double heat3d7_rt_tile(const double *__restrict__ src
     const int k0 = bz * zb, k1 = min(k0 + zb, g.nz);                      // output planes k0+1 .. k1 (padded)
     const int p0 = k0 + 1 - KK, pE = k1 + KK, pm = min(pE, g.nz + 1);
     const bool outx = lane >= H && lane < 64 - H && X <= g.nx;
-    const unsigned xo = (unsigned)min(max(X, 0), PX - 1) * 8u, xs = outx ? (unsigned)X * 8u : 0u;
+    const bool stx = outx || (FILL && ((X == 0 && bx == 0) || (X == g.nx + 1 && X <= bx * TX + TX + 1)));
+    const int z0 = FILL && k0 == 0, z1 = FILL && k1 == g.nz;  // halo planes to store
+    const unsigned xo = (unsigned)min(max(X, 0), PX - 1) * 8u, xs = stx ? (unsigned)X * 8u : 0u;
     const unsigned long long inx = __ballot(X >= 1 && X <= g.nx);
     const long long pzb = g.pz * 8, pyb = g.py * 8;
     const int up = max(w - 1, 0), dn = min(w + 1, NW - 1);  // (the outermost rows read any value)
@@ -791,7 +795,9 @@ __device__ __forceinline__ double heat3d7_rt_tile(const double *__restrict__ src
     };
     load(p0, 0);
     const int r0 = max(0, H - w * RY), r1 = min(RY, min(H + TY - w * RY, g.ny - Y0 + 1));  // output rows
-    char *out = (char *)dst + ((long long)(k0 + 1) * g.pz + (long long)Y0 * g.py) * 8;
+    const int s0 = FILL && by == 0 ? max(0, -Y0) : r0;  // rows stored
+    const int s1 = FILL && g.ny <= by * TY + TY ? min(RY, g.ny + 2 - Y0) : r1;
+    char *out = (char *)dst + ((long long)(k0 + 1 - z0) * g.pz + (long long)Y0 * g.py) * 8;
     double acc = 0.0;
     auto step = [&](const int p, const int u) {  // u = (p - p0) mod 4
         const int par = u & 1;
@@ -823,17 +829,23 @@ __device__ __forceinline__ double heat3d7_rt_tile(const double *__restrict__ src
                     L[j < KK ? j : 0][c][r] = __builtin_amdgcn_inverse_ballot_w64(rowm[r] & zin) ? v[r] : L[j - 1][c][r];
                 ex[j < KK ? j : 0][par][w][0][lane] = L[j < KK ? j : 0][c][0];
                 ex[j < KK ? j : 0][par][w][1][lane] = L[j < KK ? j : 0][c][RY - 1];
-            } else if (p >= p0 + 2 * KK) {  // plane q = k0+1 and on
-                if (outx) {
-                    if (r0 == 0 && r1 == RY) {
+            } else if (p >= p0 + 2 * KK - z0) {  // plane q = k0+1 and on
+                if constexpr (FILL) {
+                    const unsigned long long zin = q >= 1 && q <= g.nz ? ~0ull : 0ull;
+#pragma unroll
+                    for (int r = 0; r < RY; ++r)
+                        v[r] = __builtin_amdgcn_inverse_ballot_w64(rowm[r] & zin) ? v[r] : L[j - 1][c][r];
+                }
+                if (stx) {
+                    if (s0 == 0 && s1 == RY) {
 #pragma unroll
                         for (int r = 0; r < RY; ++r) buf_st_f64(plane_rsrc(out + r * pyb), xs, v[r]);
                     } else {
 #pragma unroll
                         for (int r = 0; r < RY; ++r)
-                            if (r >= r0 && r < r1) buf_st_f64(plane_rsrc(out + r * pyb), xs, v[r]);
+                            if (r >= s0 && r < s1) buf_st_f64(plane_rsrc(out + r * pyb), xs, v[r]);
                     }
-                    if (want_res) {
+                    if (want_res && outx && (!FILL || (q >= 1 && q <= g.nz))) {
 #pragma unroll
                         for (int r = 0; r < RY; ++r)
                             if (r >= r0 && r < r1) {
@@ -848,19 +860,19 @@ __device__ __forceinline__ double heat3d7_rt_tile(const double *__restrict__ src
         __syncthreads();
     };
     for (int p = p0;; p += 4) {
-        if (p > pE) break;
+        if (p > pE + z1) break;
         step(p, 0);
-        if (p + 1 > pE) break;
+        if (p + 1 > pE + z1) break;
         step(p + 1, 1);
-        if (p + 2 > pE) break;
+        if (p + 2 > pE + z1) break;
         step(p + 2, 2);
-        if (p + 3 > pE) break;
+        if (p + 3 > pE + z1) break;
         step(p + 3, 3);
     }
     return acc;
 }
 
-template <int H, int KK, int RY, int NW>
+template <int H, int KK, int RY, int NW, bool FILL>
 __global__ __launch_bounds__(64 * NW) void heat3d7_rt(const double *__restrict__ src, double *__restrict__ dst, Geom g,
                                                       double cc, double cn, int zb, int remap,
                                                       double *__restrict__ part) {
@@ -868,7 +880,7 @@ __global__ __launch_bounds__(64 * NW) void heat3d7_rt(const double *__restrict__
     __shared__ double red[kMaxWaves];
     int bx, by, bz;
     tile_coords(remap, bx, by, bz);
-    const double acc = heat3d7_rt_tile<H, KK, RY, NW>(src, dst, g, cc, cn, zb, bx, by, bz, part != nullptr, ex);
+    const double acc = heat3d7_rt_tile<H, KK, RY, NW, FILL>(src, dst, g, cc, cn, zb, bx, by, bz, part != nullptr, ex);
     if (part) {
         const double s = block_sum_f64(acc, red);
         if (threadIdx.x == 0 && threadIdx.y == 0) part[block_linear_id()] = s;
@@ -1155,8 +1167,14 @@ hipError_t h3_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
     if (h3_rt_tile(v, t)) {
         const int k = v == V_SAT3 ? a.sweeps : (v == V_SAT2 ? 2 : 1);
 #define GO(h, kk, ry, nw)                                                                                       \
-    hipLaunchKernelGGL((heat3d7_rt<h, kk, ry, nw>), grid, dim3(64, nw, 1), 0, s, src, dst, a.g, a.c[0], a.c[1], t.tz, \
-                       a.remap, a.part)
+    do {                                                                                                        \
+        if (a.fill)                                                                                             \
+            hipLaunchKernelGGL((heat3d7_rt<h, kk, ry, nw, true>), grid, dim3(64, nw, 1), 0, s, src, dst, a.g,   \
+                               a.c[0], a.c[1], t.tz, a.remap, a.part);                                          \
+        else                                                                                                    \
+            hipLaunchKernelGGL((heat3d7_rt<h, kk, ry, nw, false>), grid, dim3(64, nw, 1), 0, s, src, dst, a.g,  \
+                               a.c[0], a.c[1], t.tz, a.remap, a.part);                                          \
+    } while (0)
 #define X(h, ry, nw)                                                                                            \
     if (RT_IS(h, ry, nw, t)) {                                                                                  \
         if (k < 1 || k > h) return hipErrorInvalidValue;                                                        \
@@ -1343,6 +1361,8 @@ Tile h2_march_tile(int k, const Geom &g) {
     while (h2_nblocks(V_MARCH, best, g) > kNoallocPartials) best.ty *= 2;
     return best;
 }
+
+bool h3_fills(int v, Tile t) { return h3_rt_tile(v, t); }
 
 int h3_rt_tiles(int v, Tile *out) {
     RtShape sh[8];

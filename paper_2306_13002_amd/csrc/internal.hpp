@@ -57,6 +57,7 @@ struct SweepArgs {
     int elem_bytes;           // storage size (GENERIC: 4 or 8)
     const RtcSpec *rtc;       // GENERIC saturated: generated kernels (nullptr: table-driven kernel)
     int sweeps = 1;           // HEAT2D5 PLAIN with fused sweeps (tile.tz > 1): sweeps this launch performs
+    bool fill = false;        // HEAT3D7 register tiles: store the fixed halo too (h3_fills)
 };
 
 // Batched runs: one problem of a batch and one work item (a tile of a
@@ -89,6 +90,8 @@ struct KindOps {
 // HEAT3D7: default tile of a saturated form over one grid, or over the grids
 // of a batch class.
 Tile h3_default_tile(int variant, const std::vector<Geom> &gs);
+// HEAT3D7: whether a launch of this shape can store the destination's halo.
+bool h3_fills(int variant, Tile t);
 // POISSON19: default tile of a saturated form (V_SATURATED, V_SAT2).
 Tile p19_default_tile(int variant, const Geom &g);
 // WAVE25: default tile of the saturated form.
