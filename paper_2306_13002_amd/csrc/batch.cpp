@@ -172,7 +172,7 @@ stencil_status tune_class(const std::vector<int> &members, const std::vector<Geo
             for (int t = 0; t < T; ++t)
                 if ((err = heat3d7_ops.batch_launch(c.variant, c.tile, (const BatchProb *)d_probs,
                                                     (const BatchItem *)d_items, n, t & 1, grid,
-                                                    sweeps_per_launch(c.variant), nullptr, sc.s)) !=
+                                                    sweeps_per_launch(c.variant), false, nullptr, sc.s)) !=
                     hipSuccess)
                     return err;
             if ((err = hipEventRecord(sc.e1, sc.s)) != hipSuccess) return err;
@@ -287,7 +287,9 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
         hipStream_t s = b->side[c];
         if ((e = hipStreamWaitEvent(s, b->evs[0], 0)) != hipSuccess) return abort_capture(e, "fork wait");
         const int *members = b->d_members + C.member_base;
-        if ((e = launch_batch_copy(false, b->d_probs, members, C.n_members, C.largest, s)) != hipSuccess)
+        // register tiles store the scratch grids' halos in the first launch
+        const bool fills = h3_fills(C.run.variant, C.run.tile);
+        if (!fills && (e = launch_batch_copy(false, b->d_probs, members, C.n_members, C.largest, s)) != hipSuccess)
             return abort_capture(e, "halo copies");
         // a two-sweep class starts an odd sweep count with one single sweep; a
         // three-sweep class starts with one launch of the remainder's sweeps
@@ -297,7 +299,7 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
             const int adv = (t == 0 && rem) ? (v == V_SAT3 ? rem : 1) : sweeps_per_launch(v);
             double *part = (t + adv == T) ? b->d_part + C.item_base : nullptr;
             if ((e = p->ops->batch_launch(v, C.run.tile, b->d_probs, b->d_items + C.item_base, C.n_items, launches[c] & 1,
-                                          C.grid, adv, part, s)) != hipSuccess)
+                                          C.grid, adv, fills && t == 0, part, s)) != hipSuccess)
                 return abort_capture(e, "batch sweep");
             t += adv;
             ++launches[c];

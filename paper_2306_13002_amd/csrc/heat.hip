@@ -953,7 +953,7 @@ __global__ __launch_bounds__(RX *RY) void heat3d7_sat3_batch(const BatchProb *__
     }
 }
 
-template <int H, int KK, int RY, int NW>
+template <int H, int KK, int RY, int NW, bool FILL>
 __global__ __launch_bounds__(64 * NW) void heat3d7_rt_batch(const BatchProb *__restrict__ probs,
                                                             const BatchItem *__restrict__ items, int n_items,
                                                             int parity, int zb, double *__restrict__ part) {
@@ -962,7 +962,7 @@ __global__ __launch_bounds__(64 * NW) void heat3d7_rt_batch(const BatchProb *__r
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const BatchItem w = items[it];
         const BatchProb &Q = probs[w.prob];
-        const double acc = heat3d7_rt_tile<H, KK, RY, NW>(Q.f[parity], Q.f[parity ^ 1], Q.g, Q.cc, Q.cn, zb, w.bx,
+        const double acc = heat3d7_rt_tile<H, KK, RY, NW, FILL>(Q.f[parity], Q.f[parity ^ 1], Q.g, Q.cc, Q.cn, zb, w.bx,
                                                           w.by, w.bz, part != nullptr, ex);
         if (part) {
             const double s = block_sum_f64(acc, red);
@@ -1230,12 +1230,18 @@ hipError_t h3_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
 }
 
 hipError_t h3_batch_launch(int v, Tile t, const BatchProb *probs, const BatchItem *items, int n_items, int parity,
-                           int grid, int sweeps, double *part, hipStream_t s) {
+                           int grid, int sweeps, bool fill, double *part, hipStream_t s) {
     if (h3_rt_tile(v, t)) {
         const int k = v == V_SAT3 ? sweeps : (v == V_SAT2 ? 2 : 1);
 #define GO(h, kk, ry, nw)                                                                                        \
-    hipLaunchKernelGGL((heat3d7_rt_batch<h, kk, ry, nw>), dim3(grid), dim3(64, nw, 1), 0, s, probs, items, n_items, parity, \
-                       t.tz, part)
+    do {                                                                                                         \
+        if (fill)                                                                                                \
+            hipLaunchKernelGGL((heat3d7_rt_batch<h, kk, ry, nw, true>), dim3(grid), dim3(64, nw, 1), 0, s, probs, items, \
+                               n_items, parity, t.tz, part);                                                     \
+        else                                                                                                     \
+            hipLaunchKernelGGL((heat3d7_rt_batch<h, kk, ry, nw, false>), dim3(grid), dim3(64, nw, 1), 0, s, probs, items, \
+                               n_items, parity, t.tz, part);                                                     \
+    } while (0)
 #define X(h, ry, nw)                                                                                            \
     if (RT_IS(h, ry, nw, t)) {                                                                                  \
         if (k < 1 || k > h) return hipErrorInvalidValue;                                                        \

@@ -82,8 +82,9 @@ struct KindOps {
     // Items [0, n_items) are visited by `grid` blocks in a fixed stride; the
     // residual partial of item i goes to part[i] when part is non-null.
     // sweeps: the sweeps this launch performs (V_SAT3: 1..3; others: their own).
+    // fill: store the fixed halos too (h3_fills).
     hipError_t (*batch_launch)(int variant, Tile t, const BatchProb *probs, const BatchItem *items, int n_items,
-                               int parity, int grid, int sweeps, double *part, hipStream_t s);
+                               int parity, int grid, int sweeps, bool fill, double *part, hipStream_t s);
     int (*sat3_tiles)(Tile *out, int max);  // output tiles of the three-sweep form; nullptr if none
 };
 

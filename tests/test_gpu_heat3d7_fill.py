@@ -48,3 +48,26 @@ def test_first_launch_stores_the_halo(variant, n):
         p.run_noalloc(f, iterations=4, residual=r)
         assert torch.equal(f[0], want[0]) and torch.equal(f[1][halo], u0[halo])
         assert abs(r.item() - q.residual()) <= 1e-12 * q.residual() + 1e-300
+
+
+@pytest.mark.parametrize("variant", ["auto", "saturated_t2", "saturated_t3"])
+@pytest.mark.parametrize("T", [1, 3, 4, 5])
+def test_batch_first_launch_stores_the_halos(variant, T):
+    from paper_2306_13002_amd.stencil import BatchPlan, Plan
+    sizes = [(1, 1, 1), (59, 27, 9), (40, 90, 33), (130, 20, 64), (7, 100, 5)]
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    ins = [torch.rand([e + 2 for e in reversed(n)], dtype=torch.float64, device="cuda", generator=gen) for n in sizes]
+    fields = [(u.clone(), torch.full_like(u, float("nan"))) for u in ins]
+    with BatchPlan(sizes, coef=(0.4, 0.1), variant=variant) as p:
+        for rep in range(3):
+            for (a, s), u in zip(fields, ins):
+                a.copy_(u)
+                s.fill_(float("nan"))
+            p.run(fields, iterations=T)
+            for n, (a, s), u in zip(sizes, fields, ins):
+                h = torch.ones(u.shape, dtype=torch.bool, device="cuda")
+                h[1:-1, 1:-1, 1:-1] = False
+                with Plan("heat3d7", n, variant="saturated", coef=(0.4, 0.1), tile=(32, 8, 4)) as q:
+                    w = [u.clone(), torch.empty_like(u)]
+                    q.run(w, iterations=T)
+                assert torch.equal(a, w[0]) and torch.equal(s[h], u[h]), (rep, n)
