@@ -106,8 +106,10 @@ std::vector<Cand> tune_candidates(const KindOps *ops, int kind, const Geom &g, c
         for (const Tile &t : ft)
             if (ops->tile_ok(V_PLAIN, t) && tile_fits(t)) out.push_back({V_PLAIN, t, 0});
     }
-    // the two-sweep Poisson kernel addresses a plane with 32-bit byte offsets
-    const bool sat2_fits = kind != STENCIL_POISSON19 || g.pz * (long long)sizeof(float) <= kMaxPlaneBytes32;
+    // two sweeps per pass hold the boundary fixed between them; the Poisson
+    // kernel addresses a plane with 32-bit byte offsets
+    const bool sat2_fits = rq.bc == STENCIL_BC_DIRICHLET &&
+                           (kind != STENCIL_POISSON19 || g.pz * (long long)sizeof(float) <= kMaxPlaneBytes32);
     if ((rq.variant == V_SAT2 || rq.variant == STENCIL_AUTO) && ops->sat2_tiles && sat2_fits) {
         Tile st[64];
         const int ns = ops->sat2_tiles(st, 64);
@@ -202,12 +204,13 @@ struct Buffers {
 
 std::string tune_key(const stencil_plan_s *p, const TuneRequest &rq) {
     char buf[512];
-    // "/c8": candidate set 8 (AUTO includes the two- and three-sweep forms,
+    // "/c9": candidate set 9 (AUTO includes the two- and three-sweep forms
+    // where boundaries are fixed,
     // the latter with intermediate z-blocks; HEAT2D5 the fused plain sweeps
     // with one-cell-per-thread tiles; GENERIC tiles of 16 and 32 rows and
     // z-blocks from 4; the closest candidates re-timed); entries of earlier
     // sets are not reused
-    std::snprintf(buf, sizeof buf, "k%d/d%d/bc%d/n%dx%dx%d/r%d/py%lld/pz%lld/v%d/t%d,%d,%d,%d/h%08x/c8", p->kind,
+    std::snprintf(buf, sizeof buf, "k%d/d%d/bc%d/n%dx%dx%d/r%d/py%lld/pz%lld/v%d/t%d,%d,%d,%d/h%08x/c9", p->kind,
                   p->dtype, p->bc, p->g.nx, p->g.ny, p->g.nz, p->g.r, p->g.py, p->g.pz, rq.variant, rq.tile_x,
                   rq.tile_y, rq.zblock, rq.tile_map, p->taps_hash);
     return buf;
