@@ -186,6 +186,31 @@ std::vector<Cand> run_candidates(int kind, const Geom &g, const TuneRequest &rq)
     return out;
 }
 
+bool same_grids(int kind, int form, int run) {
+    if (kind == STENCIL_HEAT2D5) return form == V_PLAIN && run == V_MARCH;
+    auto sat = [](int v) { return v == V_SATURATED || v == V_SAT2 || v == V_SAT3; };
+    return kind == STENCIL_HEAT3D7 && sat(form) && sat(run);
+}
+
+void settle_run(int kind, const std::vector<Cand> &cands, const std::vector<std::pair<double, size_t>> &timed,
+                const std::vector<Cand> &runs, const std::vector<double> &run_us, TuneEntry *best) {
+    if (runs.empty()) return;
+    const size_t r = std::min_element(run_us.begin(), run_us.end()) - run_us.begin();
+    if (run_us[r] >= best->us) return;
+    if (!same_grids(kind, best->variant, runs[r].variant)) {
+        size_t i = 0;
+        while (i < timed.size() && !same_grids(kind, cands[timed[i].second].variant, runs[r].variant)) ++i;
+        if (i == timed.size()) return;
+        const Cand &c = cands[timed[i].second];
+        best->variant = c.variant;
+        best->tile = c.tile;
+        best->remap = c.remap;
+        best->us = timed[i].first;
+    }
+    best->run_variant = runs[r].variant;
+    best->run_tile = runs[r].tile;
+}
+
 namespace {
 
 struct Buffers {
@@ -204,13 +229,13 @@ struct Buffers {
 
 std::string tune_key(const stencil_plan_s *p, const TuneRequest &rq) {
     char buf[512];
-    // "/c9": candidate set 9 (AUTO includes the two- and three-sweep forms
-    // where boundaries are fixed,
-    // the latter with intermediate z-blocks; HEAT2D5 the fused plain sweeps
-    // with one-cell-per-thread tiles; GENERIC tiles of 16 and 32 rows and
-    // z-blocks from 4; the closest candidates re-timed); entries of earlier
-    // sets are not reused
-    std::snprintf(buf, sizeof buf, "k%d/d%d/bc%d/n%dx%dx%d/r%d/py%lld/pz%lld/v%d/t%d,%d,%d,%d/h%08x/c9", p->kind,
+    // "/c10": candidate set 10 (AUTO includes the two- and three-sweep forms
+    // where boundaries are fixed, the latter with intermediate z-blocks;
+    // HEAT2D5 the fused plain sweeps with one-cell-per-thread tiles; GENERIC
+    // tiles of 16 and 32 rows and z-blocks from 4; the closest candidates
+    // re-timed; launches only of the reported form's result); entries of
+    // earlier sets are not reused
+    std::snprintf(buf, sizeof buf, "k%d/d%d/bc%d/n%dx%dx%d/r%d/py%lld/pz%lld/v%d/t%d,%d,%d,%d/h%08x/c10", p->kind,
                   p->dtype, p->bc, p->g.nx, p->g.ny, p->g.nz, p->g.r, p->g.py, p->g.pz, rq.variant, rq.tile_x,
                   rq.tile_y, rq.zblock, rq.tile_map, p->taps_hash);
     return buf;
@@ -339,23 +364,15 @@ stencil_status tune_exhaustive(stencil_plan_s *p, const TuneRequest &rq, TuneEnt
             bestv.remap = c.remap;
         }
     }
-    // the launches that give the same results: the fastest, if it beats the pick
-    double run_us = 1e300;
-    Cand run{};
-    for (const Cand &c : run_candidates(p->kind, p->g, rq)) {
-        const double us = time_one(p, c, b, s, e0, e1, T, 3, &te);
+    const std::vector<Cand> runs = run_candidates(p->kind, p->g, rq);
+    std::vector<double> run_us;
+    for (const Cand &c : runs) {
+        run_us.push_back(time_one(p, c, b, s, e0, e1, T, 3, &te));
         if (te != hipSuccess) return hip_fail(te, "tuner launch");
         logf("tune kind=%d launches v=%d tile=(%d,%d,%d): %.2f us/sweep", p->kind, c.variant, c.tile.tx, c.tile.ty,
-             c.tile.tz, us);
-        if (us < run_us) {
-            run_us = us;
-            run = c;
-        }
+             c.tile.tz, run_us.back());
     }
-    if (run_us < bestv.us) {
-        bestv.run_variant = run.variant;
-        bestv.run_tile = run.tile;
-    }
+    settle_run(p->kind, cands, timed, runs, run_us, &bestv);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     *best = bestv;
     return STENCIL_OK;

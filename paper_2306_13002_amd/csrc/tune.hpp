@@ -2,6 +2,7 @@
 #pragma once
 
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/stencil.h"
@@ -31,9 +32,9 @@ struct TuneEntry {
     int variant;  // V_PLAIN, V_SATURATED, V_SAT2 or V_SAT3
     Tile tile;
     int remap;    // 0 natural, 1 XCD-chunked
-    double us;    // median time per sweep of the winner
+    double us;    // median time per sweep of (variant, tile)
     // what the plan launches instead where that is faster still with the same
-    // results (HEAT3D7 register tiles); run_variant < 0: nothing
+    // results (settle_run); run_variant < 0: nothing
     int run_variant = -1;
     Tile run_tile{};
 };
@@ -62,6 +63,16 @@ std::vector<Cand> tune_candidates(const KindOps *ops, int kind, const Geom &g, c
 // Launches the tuners time beside the candidates of a request that leaves the
 // shape open (see TuneEntry::run_variant).
 std::vector<Cand> run_candidates(int kind, const Geom &g, const TuneRequest &rq);
+// Whether launches of form `run` leave the grids of reported form `form` bit
+// for bit: HEAT2D5 PLAIN runs may march, the saturated HEAT3D7 forms stand for
+// each other; PLAIN adds in another order than those.
+bool same_grids(int kind, int form, int run);
+// Let the fastest of the timed launches (us, index into runs) replace what
+// `best` launches if it is faster.  A pick of another result gives way to the
+// fastest timed candidate (sorted by us) of the launch's result, so that the
+// plan reports a form whose grids it produces.
+void settle_run(int kind, const std::vector<Cand> &cands, const std::vector<std::pair<double, size_t>> &timed,
+                const std::vector<Cand> &runs, const std::vector<double> &run_us, TuneEntry *best);
 void cost_features(const StencilInfo &si, const Cand &c, float out[24]);
 stencil_status tune_model(stencil_plan_s *p, const TuneRequest &rq, TuneEntry *best);
 
