@@ -441,7 +441,7 @@ stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d) {
         TuneRequest rq{has_sat ? dv : (int)STENCIL_PLAIN, d->tile_x, d->tile_y, d->zblock, d->tile_map, d->bc};
         const std::string key = tune_key(p, rq);
         TuneEntry e{};
-        if (!tune_lookup(key, &e)) {
+        if (!tune_lookup(key, ops, p->kind, rq, &e)) {
             stencil_status st = tune_exhaustive(p, rq, &e);
             if (st != STENCIL_OK) return st;
             tune_store(key, e);

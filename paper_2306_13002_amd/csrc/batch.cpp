@@ -446,7 +446,7 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
             const TuneRequest rq{d.variant, d.tile_x, d.tile_y, d.zblock, 1};
             const std::string key = class_key(members, geoms, rq);
             TuneEntry te{};
-            if (tune_lookup(key, &te)) {
+            if (tune_lookup(key, &heat3d7_ops, STENCIL_HEAT3D7, rq, &te)) {
                 tuned = true;
             } else {
                 st = tune_class(members, geoms, ds[rep[c]].coef[0], ds[rep[c]].coef[1], rq, &te);

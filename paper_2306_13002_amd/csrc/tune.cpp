@@ -241,11 +241,39 @@ std::string tune_key(const stencil_plan_s *p, const TuneRequest &rq) {
     return buf;
 }
 
-bool tune_lookup(const std::string &key, TuneEntry *out) {
+// Whether a tuner could have made this entry for the request: a launch shape
+// that is not offered would divide by zero or fail at every launch.
+static bool entry_offered(const KindOps *ops, int kind, const TuneRequest &rq, const TuneEntry &e) {
+    const bool fixed = rq.bc == STENCIL_BC_DIRICHLET;
+    auto form_ok = [&](int v) {
+        switch (v) {
+        case V_PLAIN: return true;
+        case V_SATURATED: return ops->sat_tiles != nullptr;
+        case V_SAT2: return ops->sat2_tiles && fixed;
+        case V_SAT3: return ops->sat3_tiles && fixed;
+        default: return false;
+        }
+    };
+    const Tile &t = e.tile;
+    if (!form_ok(e.variant) || (rq.variant != STENCIL_AUTO && rq.variant != e.variant) || !ops->tile_ok(e.variant, t) ||
+        (rq.tile_x && rq.tile_x != t.tx) || (rq.tile_y && rq.tile_y != t.ty) || (rq.zblock && rq.zblock != t.tz) ||
+        (launch_sweeps(kind, e.variant, t) > 1 && !fixed))
+        return false;
+    if (e.run_variant < 0) return true;
+    if (rq.tile_x || rq.tile_y || rq.zblock || !same_grids(kind, e.variant, e.run_variant)) return false;
+    if (e.run_variant == V_MARCH) return fixed;
+    return form_ok(e.run_variant) && ops->tile_ok(e.run_variant, e.run_tile);
+}
+
+bool tune_lookup(const std::string &key, const KindOps *ops, int kind, const TuneRequest &rq, TuneEntry *out) {
     std::lock_guard<std::mutex> lk(g_mu);
     load_file_locked();
     auto it = g_cache.find(key);
     if (it == g_cache.end()) return false;
+    if (!entry_offered(ops, kind, rq, it->second)) {
+        logf("tune cache: entry of %s is not offered; tuning again", key.c_str());
+        return false;
+    }
     *out = it->second;
     return true;
 }

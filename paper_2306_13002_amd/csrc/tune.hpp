@@ -77,7 +77,9 @@ void cost_features(const StencilInfo &si, const Cand &c, float out[24]);
 stencil_status tune_model(stencil_plan_s *p, const TuneRequest &rq, TuneEntry *best);
 
 std::string tune_key(const stencil_plan_s *p, const TuneRequest &rq);
-bool tune_lookup(const std::string &key, TuneEntry *out);
+// The cached pick of a request, if there is one and what it names is offered
+// (entries may come from a file).
+bool tune_lookup(const std::string &key, const KindOps *ops, int kind, const TuneRequest &rq, TuneEntry *out);
 void tune_store(const std::string &key, const TuneEntry &e);
 stencil_status tune_exhaustive(stencil_plan_s *p, const TuneRequest &rq, TuneEntry *best);
 
