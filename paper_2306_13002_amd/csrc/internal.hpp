@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "common.hpp"
@@ -132,6 +133,15 @@ hipError_t launch_stream(int op, const double *a, const double *b, const double 
                          int width, int flags, int grid, hipStream_t s);
 
 inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
+
+// Blocks per problem of a batch's copy launches (launch_batch_copy): about
+// eight elements per thread of the largest grid, at most 1024, and few enough
+// that n problems make at most 2^23 blocks (a launch holds fewer than 2^32
+// threads; the blocks stride over what is left).
+inline int batch_copy_chunks(bool tail, long long n, long long largest) {
+    const long long want = cdiv(tail ? largest : largest / 8, 2048), most = (1LL << 23) / n;
+    return (int)std::max(1LL, std::min({want, most, 1024LL}));
+}
 
 // Largest plane (pitch_z * element size, bytes) that a kernel addressing a
 // plane with 32-bit byte offsets through a buffer resource accepts.

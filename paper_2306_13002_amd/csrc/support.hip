@@ -256,9 +256,7 @@ hipError_t launch_interior_copy(const void *src, void *dst, int eb, const Geom &
 // Copies of n grids of a batch, the largest of `largest` interior cells.
 hipError_t launch_batch_copy(bool tail, const BatchProb *probs, const int *members, int n, long long largest,
                              hipStream_t s) {
-    // about eight elements per thread; the grid stays below 2^31 blocks for 2^20 problems
-    const long long work = tail ? largest : largest / 8;
-    const int chunks = (int)std::max(1LL, std::min(cdiv(work, 2048), 1024LL));
+    const int chunks = batch_copy_chunks(tail, n, largest);
     const dim3 grid((unsigned)n * (unsigned)chunks);
     const bool w = largest < kIndex32;
     if (tail) {
