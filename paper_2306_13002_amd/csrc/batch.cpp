@@ -472,10 +472,12 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
             if ((st = stencil_plan(&d, &rp)) != STENCIL_OK) break;
             C.variant = rp->variant;
             C.tile = rp->tile;
+            // tuned on the largest problem alone: what that plan launches
+            if (d.tune != STENCIL_TUNE_FIXED) C.run = Launch{rp->many.variant, rp->many.tile};
             free_plan(rp);
         }
         if (C.run.tile.tx == 0) C.run = Launch{C.variant, C.tile};
-        if (!tuned && C.variant != V_PLAIN && !d.tile_x && !d.tile_y && !d.zblock) {
+        if (!tuned && d.tune == STENCIL_TUNE_FIXED && C.variant != V_PLAIN && !d.tile_x && !d.tile_y && !d.zblock) {
             // the defaults' launches, as for single plans (default_launches),
             // over the whole class: its problems fill the chip together
             std::vector<Geom> gs;
