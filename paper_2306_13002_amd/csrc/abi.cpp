@@ -390,15 +390,18 @@ void default_launches(stencil_plan_s *p, const stencil_desc *d, int requested) {
     if (d->tile_map) p->one.remap = p->many.remap = p->remap;  // the caller's tile order
 }
 
-// The launch shape of a run of `iterations` sweeps.  Marching HEAT2D5 runs
-// take an even number of launches (the result then ends in fields[0] without
-// a copy back) of at most kMarchMax sweeps, as equal as they can be.
+// Launches of a marching HEAT2D5 run: an even number (the result then ends in
+// fields[0] without a copy back), as few as kMarchMax sweeps each allow.
+int march_launches(int iterations) {
+    return 2 * ((iterations - 1) / (2 * kMarchMax) + 1);
+}
+
+// The launch shape of a run of `iterations` sweeps.
 Launch run_launch(const stencil_plan_s *p, int iterations) {
     if (iterations <= 1) return p->one;
     if (!p->march) return p->many;
     if (iterations == 2) return p->one;  // marching one sweep at a time is slower than the plain kernel
-    const int half = (iterations + 2 * kMarchMax - 1) / (2 * kMarchMax);
-    Launch l{V_MARCH, h2_march_tile((int)cdiv(iterations, 2LL * half), p->g)};
+    Launch l{V_MARCH, h2_march_tile((int)cdiv(iterations, march_launches(iterations)), p->g)};
     l.nblocks = p->ops->nblocks(l.variant, l.tile, p->g);
     return l;
 }
@@ -544,7 +547,7 @@ hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int i
     // sweeps per launch: the two-sweep form does two (an odd count starts with
     // one single-sweep launch); fused HEAT2D5 sweeps do tile.tz and the
     // three-sweep form three (the first launch takes the remainder of the
-    // count)
+    // count); marching sweeps share the count among an even number of launches
     const int per = launch_sweeps(p->kind, l.variant, l.tile);
     const bool fused = (p->kind == STENCIL_HEAT2D5 && per > 1) || l.variant == V_SAT3 || l.variant == V_MARCH;
     hipError_t e;
@@ -554,7 +557,11 @@ hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int i
             return e;
         const int first = iterations % per;
         const int v = (!fused && t == 0 && first) ? V_SATURATED : l.variant;
-        const int adv = fused ? (t == 0 && first ? first : per) : sweeps_per_launch(v);
+        // marching launches share the count as equally as they can (a tile
+        // of k sweeps runs k - 1 too)
+        const int adv = l.variant == V_MARCH ? (int)cdiv(iterations - t, march_launches(iterations) - *launches)
+                        : fused              ? (t == 0 && first ? first : per)
+                                             : sweeps_per_launch(v);
         a.sweeps = adv;
         a.remap = l.remap;
         a.fill = t == 0 && first_fills(p, l);
