@@ -1303,6 +1303,23 @@ hipError_t h3_batch_launch(int v, Tile t, const BatchProb *probs, const BatchIte
 
 }  // namespace
 
+// The same estimate (see h3_default_tile) for the nominal LDS tile, 32 x 8 x 8,
+// which wins where a narrow grid leaves most of 64 lanes idle or a flat one most
+// rows: us per sweep, its and the register tile's, 20x300x300 9.8 and 12.1,
+// 64x300x300 18.4 and 19.7, but 36x300x300 15.0 and 12.5, 20x100x100 5.4 and
+// 4.1; in pairs 20x3x4000 4.4 and 5.1, but 20x300x300 8.3 and 7.9.  Three
+// sweeps per pass: never by 5 %.
+double h3_lds_estimate(int v, Tile t, const std::vector<Geom> &gs) {
+    long long blocks = 0;
+    for (const Geom &g : gs) blocks += cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, t.tz);
+    // per step and per wave of a SIMD, and the share that waits at the barrier,
+    // in the units of h3_default_tile; four waves a block (pairs: six)
+    const bool pair = v == V_SAT2;
+    const double step = pair ? 249 : 157, waves = pair ? 1.5 : 1, idle = pair ? 1.5 : 1.91;
+    const double per_cu = (double)cdiv(blocks, 256), res = std::min(per_cu, pair ? 2.0 : 4.0);
+    return per_cu / res * (t.tz + (pair ? 4 : 2)) * step * (res * waves + idle);
+}
+
 // Default tile of a saturated form over one grid or the grids of a batch
 // class: the register tile and z-block with the lowest estimate of
 //   rounds * (planes + 2 sweeps) * cycles per step * (waves per SIMD + 0.7),
@@ -1314,8 +1331,9 @@ hipError_t h3_batch_launch(int v, Tile t, const BatchProb *probs, const BatchIte
 // (58x26x2 8.7, 58x10x8 9.4); 400^3 58x26x16 257 (x8 277, x32 270: the
 // blocks of a longer march drift apart, and rows at their borders leave
 // the L2 half written); 64 grids of edges 32 to 160, the largest class
-// 58x26x16 (326 us for all; 58x42x16 344, 58x26x8 355).  One sweep: 400^3 62x14x8 233 (x16 246, x32 268);
-// 54^3 62x14x2 3.2 (x8 4.8).
+// 58x26x16 (326 us for all; 58x42x16 344, 58x26x8 355).  One sweep: 400^3
+// 62x14x8 233 (x16 246, x32 268); 54^3 62x14x2 3.2 (x8 4.8).  Narrow and flat
+// grids: h3_lds_estimate.
 Tile h3_default_tile(int v, const std::vector<Geom> &gs) {
     RtShape sh[8];
     const int n = h3_rt_shapes(v, sh), sweeps = sweeps_per_launch(v);
@@ -1341,6 +1359,10 @@ Tile h3_default_tile(int v, const std::vector<Geom> &gs) {
                 best = Tile{tx, ty, zb};
             }
         }
+    }
+    if (v != V_SAT3) {
+        const Tile lds{32, 8, std::min(8, deepest)};
+        if (h3_lds_estimate(v, lds, gs) < cost) best = lds;
     }
     return best;
 }
