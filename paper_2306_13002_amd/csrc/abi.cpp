@@ -399,6 +399,14 @@ int march_launches(int iterations) {
 // The launch shape of a run of `iterations` sweeps.
 Launch run_launch(const stencil_plan_s *p, int iterations) {
     if (iterations <= 1) return p->one;
+    // AUTO HEAT3D7 runs of two sweeps: one launch of several sweeps leaves the
+    // result in the scratch grid, and the copy back costs more than a second
+    // launch while the Infinity Cache (256 MB) holds both grids (us per call, the
+    // copied launch and two launches: 128^3 25.0 and 18.3, 160^3 31 and 25.5,
+    // 100 x 200 x 300 43 and 38; 256^3 113 and 116, 400^3 439 and 462)
+    if (iterations == 2 && p->many.variant == V_SAT3 && p->one.variant == V_SATURATED &&
+        2 * span_elems(p) * (long long)sizeof(double) <= (256LL << 20))
+        return p->one;
     if (!p->march) return p->many;
     if (iterations == 2) return p->one;  // marching one sweep at a time is slower than the plain kernel
     Launch l{V_MARCH, h2_march_tile((int)cdiv(iterations, march_launches(iterations)), p->g)};
