@@ -3,18 +3,20 @@
 //
 // This is the paper's code-generation step (Sec. Code Generation) done at
 // run time for the taps a plan was given: the saturated expression -- taps
-// grouped by coefficient id and z offset, each group summed as a balanced
-// tree in ascending address order, one FMA per group -- is emitted as
-// straight-line HIP with compile-time LDS offsets and exact coefficient
-// literals, wrapped around the streaming body every generic kernel shares
-// (generic_body.hpp), and compiled for the device.  Modules are cached per
-// source text in-process and, when STENCIL_RTC_CACHE names a directory, as
-// code-object files there.  rtc_function serves every generated kernel of
-// the library (also the saturator's programs).
+// grouped by coefficient id and z offset, each group summed before it is
+// multiplied, the sums shared among rows and planes, or one FMA per tap where
+// sharing saves little (SlotEmitter, emit_plan) -- is emitted as straight-line
+// HIP with compile-time LDS offsets and exact coefficient literals, wrapped
+// around the streaming body every generic kernel shares (generic_body.hpp), and
+// compiled for the device.  Modules are cached per source text in-process and,
+// when STENCIL_RTC_CACHE names a directory, as code-object files there.
+// rtc_function serves every generated kernel of the library (also the
+// saturator's programs).
 #include <hip/hip_runtime.h>
 #include <hip/hiprtc.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -43,6 +45,18 @@ unsigned long long fnv64(const std::string &s) {
     unsigned long long h = 1469598103934665603ull;
     for (unsigned char c : s) h = (h ^ c) * 1099511628211ull;
     return h;
+}
+
+// Whether by_planes keeps a sum for slot s: it pays for two taps or more (of the
+// centre column: where the plane has others too).
+bool plane_sum(const RtcSpec &sp, int s, bool centre) {
+    int mid = 0, n = 0;
+    for (const RtcGroup &gr : sp.slots[s])
+        for (const auto &t : gr.taps) {
+            ++n;
+            mid += t.first == 0;
+        }
+    return centre ? mid > 1 && n > mid : n > 1;
 }
 
 // Emits one plane's contributions to the accumulator queue for every row of
@@ -131,9 +145,12 @@ struct SlotEmitter {
         return buf;
     }
     // acc of slot s += c * v for row m (the queue starts each slot at 0)
-    void fma_into(int s, int m, double c, const std::string &v) {
+    std::string acc_name(int s, int m) const {
         const int w = 2 * sp.R + 1;
-        const std::string dst = "acc[" + std::to_string((s - phase + w) % w) + "][" + std::to_string(m) + "]";
+        return "acc[" + std::to_string((s - phase + w) % w) + "][" + std::to_string(m) + "]";
+    }
+    void fma_into(int s, int m, double c, const std::string &v) {
+        const std::string dst = acc_name(s, m);
         o += "        " + dst + " = fma(" + lit(c) + ", " + v + ", " + dst + ");\n";
         ++n_fma;
     }
@@ -156,14 +173,17 @@ struct SlotEmitter {
             o += "        }\n";
         }
     }
-    // Column by column of the window, one FMA per tap, each coefficient used
-    // for all the thread's rows at once: for patterns whose sums do not repeat.
-    void by_taps() {
+    // The taps for which `takes` holds, column by column of the window, so that
+    // a column's cells are all that is held; each coefficient is used for all
+    // the thread's rows at once, one FMA per tap and row by fma(slot, row, dx, ...).
+    template <class Takes, class Fma>
+    void by_columns(Takes takes, Fma fma) {
         const int R = sp.R, w = 2 * R + 1, NQ = 2 * R + 1;
         std::vector<std::vector<std::vector<double>>> c(NQ, std::vector<std::vector<double>>(w * w));
         for (int s = 0; s < NQ; ++s)
             for (const RtcGroup &gr : sp.slots[s])
-                for (const auto &t : gr.taps) c[s][(t.second + R) * w + t.first + R].push_back(gr.coef);
+                for (const auto &t : gr.taps)
+                    if (takes(gr)) c[s][(t.second + R) * w + t.first + R].push_back(gr.coef);
         for (int dx = 0; dx < w; ++dx) {
             for (int dy = 0; dy < w; ++dy)
                 for (int s = 0; s < NQ; ++s)
@@ -174,10 +194,63 @@ struct SlotEmitter {
                     for (double v : c[s][dy * w + dx]) {
                         if (!any) guard(s);
                         any = true;
-                        for (int m = 0; m < RY; ++m) fma_into(s, m, v, cell(dx - R, m + dy));
+                        for (int m = 0; m < RY; ++m) fma(s, m, dx - R, v, cell(dx - R, m + dy));
                     }
                 if (any) o += "        }\n";
             }
+        }
+    }
+    // For patterns whose sums do not repeat: one FMA per tap into its slot.
+    void by_taps() {
+        by_columns([](const RtcGroup &) { return true; },
+                   [this](int s, int m, int, double c, const std::string &v) { fma_into(s, m, c, v); });
+    }
+    // ... in the written order of rounding: the groups of one tap by columns,
+    // then row by row and slot by slot the groups of several, each a tree and
+    // one FMA.
+    void by_groups() {
+        const int R = sp.R, NQ = 2 * R + 1;
+        by_columns([](const RtcGroup &gr) { return gr.taps.size() == 1; },
+                   [this](int s, int m, int, double c, const std::string &v) { fma_into(s, m, c, v); });
+        for (int m = 0; m < RY; ++m)
+            for (int s = 0; s < NQ; ++s) {
+                bool any = false;
+                for (const RtcGroup &gr : sp.slots[s])
+                    for (const auto &t : gr.taps)
+                        if (gr.taps.size() > 1) {
+                            cell(t.first, m + R + t.second);
+                            any = true;
+                        }
+                if (!any) continue;
+                guard(s);
+                const std::map<std::string, std::string> outer = memo;  // names made inside the guard end with it
+                for (const RtcGroup &gr : sp.slots[s])
+                    if (gr.taps.size() > 1) fma_into(s, m, gr.coef, sum(gr, m));
+                memo = outer;
+                o += "        }\n";
+            }
+    }
+    // ... and with one sum per plane, or (centre) one for the taps of a plane's
+    // centre column: an FMA per tap into a sum that starts at 0 with the plane
+    // and is added to the slot once; the other taps straight into the slot.
+    // Holds a column's cells where trees hold the window's.
+    void by_planes(bool centre) {
+        const int NQ = 2 * sp.R + 1;
+        std::vector<char> sums(NQ);
+        for (int s = 0; s < NQ; ++s) sums[s] = plane_sum(sp, s, centre);
+        auto part = [](int s, int m) { return "p" + std::to_string(s) + "_" + std::to_string(m); };
+        for (int s = 0; s < NQ; ++s)
+            for (int m = 0; m < RY && sums[s]; ++m) o += "        double " + part(s, m) + " = 0.0;\n";
+        by_columns([](const RtcGroup &) { return true; },
+                   [&](int s, int m, int dx, double c, const std::string &v) {
+                       if (!sums[s] || (centre && dx)) return fma_into(s, m, c, v);
+                       o += "        " + part(s, m) + " = fma(" + lit(c) + ", " + v + ", " + part(s, m) + ");\n";
+                   });
+        for (int s = 0; s < NQ; ++s) {
+            if (!sums[s]) continue;
+            guard(s);
+            for (int m = 0; m < RY; ++m) o += "        " + acc_name(s, m) + " += " + part(s, m) + ";\n";
+            o += "        }\n";
         }
     }
 };
@@ -189,7 +262,7 @@ namespace {
 // How a stencil's plane arithmetic is emitted for RY rows per thread.
 struct EmitPlan {
     int ry;
-    bool share;     // group sums shared among the slots (by_sums), else one FMA per tap (by_taps)
+    enum { SUMS, TAPS, PLANES, CENTRES, GROUPS } order;  // by_sums, by_taps, by_planes, by_groups
     int per_plane;  // FP64 instructions per thread and plane
     bool rotate;    // the accumulator queue moves on by name
     bool guarded;   // slots that are not live are skipped
@@ -230,6 +303,50 @@ struct SpecEntry {
 };
 std::map<std::string, SpecEntry> g_specs;  // guarded by g_mu
 
+// Squares of the rounded values' magnitudes, summed over the roundings of one
+// output, with every cell at 1 (the mean square of the error up to a factor):
+// the tap sums as written -- per plane and coefficient a balanced tree and one
+// FMA -- and by_planes' two orders.
+struct Rounding {
+    double groups = 0, planes = 0, centres = 0;
+};
+double tree_rounding(double c, size_t n) {
+    if (n < 2) return 0;
+    const size_t m = (n + 1) / 2;
+    return c * c * n * n + tree_rounding(c, m) + tree_rounding(c, n - m);
+}
+double plane_rounding(const RtcSpec &sp, bool centre) {
+    double e = 0, acc = 0;
+    for (int s = 0; s < (int)sp.slots.size(); ++s) {
+        const bool sums = plane_sum(sp, s, centre);
+        double part = 0;
+        for (int dx = -sp.R; dx <= sp.R; ++dx)  // a column at a time
+            for (const RtcGroup &gr : sp.slots[s])
+                for (const auto &t : gr.taps) {
+                    if (t.first != dx) continue;
+                    double &h = sums && !(centre && dx) ? part : acc;
+                    h += std::fabs(gr.coef);
+                    e += h * h;
+                }
+        acc += part;
+        if (sums) e += acc * acc;
+    }
+    return e;
+}
+Rounding rounding(const RtcSpec &sp) {
+    Rounding e;
+    double acc = 0;
+    for (const auto &sl : sp.slots)
+        for (const RtcGroup &gr : sl) {
+            const double c = std::fabs(gr.coef);
+            acc += c * gr.taps.size();
+            e.groups += acc * acc + tree_rounding(c, gr.taps.size());
+        }
+    e.planes = plane_rounding(sp, false);
+    e.centres = plane_rounding(sp, true);
+    return e;
+}
+
 EmitPlan emit_plan(RtcSpec &sp, int ry) {
     const std::string &key = spec_key(sp);
     {
@@ -248,8 +365,24 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
     p.ry = ry;
     // The shared sums win where they save at least a tenth of one FMA per tap
     // (a symmetric box of radius 3: 100 instead of 343 instructions per point).
-    p.share = 10 * (er.n_add + er.n_fma) <= 9 * ry * taps;
-    p.per_plane = p.share ? er.n_add + er.n_fma : ry * taps;
+    // One FMA per tap where that is the written order too (no coefficient
+    // repeats in a plane) and for F32 storage, whose rounding of the result (at
+    // 2^-24) hides the sums'.  Otherwise the order that rounds no more than the
+    // written one: rms error against it, 10 coefficients drawn for a box, sums
+    // per plane 0.52 at r = 2 and 0.49 at r = 4 (one FMA per tap 1.8 and 2.8),
+    // a star r = 4 with a sum for its centre column 0.99.  us per sweep, one
+    // FMA per tap, trees and this: those boxes at 256 x 200 x 160 54, 53, 55 and
+    // 239, 319, 251; the star at 321 x 190 x 257 80, 82, 79.
+    const Rounding err = rounding(sp);
+    bool single = true;
+    for (const auto &sl : sp.slots)
+        for (const RtcGroup &g : sl) single &= g.taps.size() == 1;
+    p.order = 10 * (er.n_add + er.n_fma) <= 9 * ry * taps ? EmitPlan::SUMS
+              : single || sp.eb == 4                      ? EmitPlan::TAPS
+              : err.planes <= err.groups                  ? EmitPlan::PLANES
+              : err.centres <= err.groups                 ? EmitPlan::CENTRES
+                                                          : EmitPlan::GROUPS;
+    p.per_plane = p.order == EmitPlan::SUMS ? er.n_add + er.n_fma : ry * taps;
     // The rotating queue repeats the plane's arithmetic 2R+1 times: taken up
     // to 4096 FP64 instructions (32 KB of the 64 KB instruction cache).
     p.rotate = p.per_plane * (2 * sp.R + 1) <= 4096;
@@ -299,7 +432,7 @@ Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
             if (zb > 2 && zb >= 2 * g.nz) break;
             if (zb < 2 * sp.R && !ep.guarded && beyond_l2 && zb < g.nz) continue;
             const double per_cu = (double)cdiv(cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, zb), 256);
-            const double out = std::min(zb, g.nz), planes = out + 2 * sp.R, live = ep.guarded && !ep.share ? out : planes;
+            const double out = std::min(zb, g.nz), planes = out + 2 * sp.R, live = ep.guarded && ep.order != EmitPlan::SUMS ? out : planes;
             const double block = live * 7 * ep.per_plane + planes * (150 + 250 * staged) + out * gr.ry * 60;
             const double est = block * (per_cu * waves / 4 + 0.7);
             if (cost == 0 || est < cost) {
@@ -327,8 +460,10 @@ std::string rtc_generic_source(RtcSpec &sp, int TX, int TY) {
     for (int ph = 0; ph < (ep.rotate ? 2 * R + 1 : 1); ++ph) {
         SlotEmitter em(sp, gr.ry, W, ph);
         em.guarded = ep.guarded;
-        if (ep.share) em.by_sums();
-        else em.by_taps();
+        if (ep.order == EmitPlan::SUMS) em.by_sums();
+        else if (ep.order == EmitPlan::TAPS) em.by_taps();
+        else if (ep.order == EmitPlan::GROUPS) em.by_groups();
+        else em.by_planes(ep.order == EmitPlan::CENTRES);
         std::snprintf(buf, sizeof buf, "        if constexpr (PH == %d) {\n", ph);
         o += buf + em.o + "        }\n";
     }
