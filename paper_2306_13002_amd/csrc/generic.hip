@@ -69,30 +69,34 @@ struct TableSlots {
             for (int m = 0; m < RY; ++m) a[m] = acc[s][m];
             for (int gi = g0; gi < g1; ++gi) {
                 const int t0 = tab.g_t[gi], t1 = tab.g_t[gi + 1];
-                // the group's taps (ascending address): alternately into two
-                // partial sums per row, then one FMA
-                double s0[RY], s1[RY];
+                // the group's taps (ascending address), eight at a time, into
+                // four partial sums per row, then one FMA
+                double p[4][RY];
 #pragma unroll
-                for (int m = 0; m < RY; ++m) s0[m] = s1[m] = 0.0;
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int m = 0; m < RY; ++m) p[q][m] = 0.0;
+                auto at = [&](int ti) {
+                    const int xy = tab.t_xy[ti];
+                    return t + me + (xy >> 16) * W + (short)(xy & 0xFFFF);
+                };
                 int ti = t0;
-                for (; ti + 2 <= t1; ti += 2) {
-                    const int xa = tab.t_xy[ti], xb = tab.t_xy[ti + 1];
-                    const double *pa = t + me + (xa >> 16) * W + (short)(xa & 0xFFFF);
-                    const double *pb = t + me + (xb >> 16) * W + (short)(xb & 0xFFFF);
+                for (; ti + 8 <= t1; ti += 8) {
 #pragma unroll
-                    for (int m = 0; m < RY; ++m) {
-                        s0[m] += pa[m * W];
-                        s1[m] += pb[m * W];
+                    for (int q = 0; q < 4; ++q) {
+                        const double *pa = at(ti + q), *pb = at(ti + q + 4);
+#pragma unroll
+                        for (int m = 0; m < RY; ++m) p[q][m] += pa[m * W] + pb[m * W];
                     }
                 }
-                if (ti < t1) {
-                    const int xa = tab.t_xy[ti];
-                    const double *pa = t + me + (xa >> 16) * W + (short)(xa & 0xFFFF);
+                for (; ti < t1; ++ti) {
+                    const double *pa = at(ti);
 #pragma unroll
-                    for (int m = 0; m < RY; ++m) s0[m] += pa[m * W];
+                    for (int m = 0; m < RY; ++m) p[0][m] += pa[m * W];
                 }
 #pragma unroll
-                for (int m = 0; m < RY; ++m) a[m] = fma(tab.g_c[gi], s0[m] + s1[m], a[m]);
+                for (int m = 0; m < RY; ++m)
+                    a[m] = fma(tab.g_c[gi], (p[0][m] + p[1][m]) + (p[2][m] + p[3][m]), a[m]);
             }
 #pragma unroll
             for (int m = 0; m < RY; ++m) acc[s][m] = a[m];
