@@ -269,14 +269,13 @@ struct EmitPlan {
     bool narrow;    // F32 storage: the LDS tile holds F32, widened at each read
 };
 
-// What a kernel's source depends on besides its tile, as text.
+// What a kernel's source depends on besides its tile and wide_rows, as text.
 const std::string &spec_key(RtcSpec &sp) {
     if (!sp.key.empty()) return sp.key;
     std::string k;
     auto put = [&k](const void *v, size_t n) { k.append((const char *)v, n); };
     const int head[3] = {sp.R, sp.eb, sp.corners};
     put(head, sizeof head);
-    put(&sp.row_bytes, sizeof sp.row_bytes);
     for (const auto &sl : sp.slots) {
         const int n = (int)sl.size();
         put(&n, sizeof n);
@@ -293,13 +292,17 @@ const std::string &spec_key(RtcSpec &sp) {
     return sp.key = k;
 }
 
+// Whether a tile's rows span too much for 32-bit lane offsets.
+bool wide_rows(const RtcSpec &sp, int TY) { return (TY + 2 * sp.R) * sp.row_bytes >= 0xFFFFFFF0LL; }
+
 // Per stencil of the process: how it is emitted, and its kernels per tile and
 // device.  A plan of a stencil that another plan has compiled takes both from
 // here instead of emitting the source again (0.3 to 3 ms).  Entries stay as
-// long as the modules do, and there are no more of them.
+// long as the modules do, and there are no more of them: grids of other
+// extents and pitches share them.
 struct SpecEntry {
     std::vector<EmitPlan> emit;
-    std::map<std::vector<int>, hipFunction_t> fn;  // tx, ty, device
+    std::map<std::vector<int>, hipFunction_t> fn;  // tx, ty, device, wide_rows
 };
 std::map<std::string, SpecEntry> g_specs;  // guarded by g_mu
 
@@ -482,11 +485,16 @@ std::string rtc_generic_source(RtcSpec &sp, int TX, int TY) {
                   "    const double sacc = stn::generic_rows_body<%s, %d, %d, %d, %d, %s, %s>(src, dst, g, zb, bx, by, bz, "
                   "part != nullptr, GenSlots{}, tile);\n",
                   T, R, TX, gr.by, gr.ry, sp.corners ? "true" : "false",
-                  (TY + 2 * R) * sp.row_bytes < 0xFFFFFFF0LL ? "unsigned" : "unsigned long long");
+                  wide_rows(sp, TY) ? "unsigned long long" : "unsigned");
     o += buf;
     o += "    if (part) {\n        const double s = stn::block_sum_f64(sacc, red);\n";
     o += "        if (threadIdx.x == 0 && threadIdx.y == 0) part[stn::block_linear_id()] = s;\n    }\n}\n";
     return o;
+}
+
+size_t rtc_stencils() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    return g_specs.size();
 }
 
 // Compile (or fetch from the caches) kernel `kernel` of source `src`;
@@ -574,7 +582,7 @@ bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     const std::string &key = spec_key(sp);
-    auto at = [&](size_t i) { return std::vector<int>{uniq[i].tx, uniq[i].ty, dev}; };
+    auto at = [&](size_t i) { return std::vector<int>{uniq[i].tx, uniq[i].ty, dev, wide_rows(sp, uniq[i].ty)}; };
     std::vector<size_t> todo;
     {
         std::lock_guard<std::mutex> lk(g_mu);

@@ -49,6 +49,8 @@ hipFunction_t rtc_function(const std::string &src, const char *kernel);
 // The tile a plan takes when its descriptor leaves it open (FIXED tuning).
 Tile rtc_default_tile(RtcSpec &sp, const Geom &g);
 std::string rtc_generic_source(RtcSpec &sp, int TX, int TY);
+// Stencils the process holds emission plans and kernels of.
+size_t rtc_stencils();
 // Compile the generated kernels of the given tiles (concurrently) and keep
 // them in sp.kernels; false if any failed.
 bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles);
