@@ -661,7 +661,7 @@ stencil_status stencil_plan(const stencil_desc *d, stencil_plan_t *out) {
         return st;
     }
     if (p->kind == STENCIL_GENERIC && p->variant == V_SATURATED && p->base_args.rtc &&
-        !rtc_prepare(*p->rtc, {p->tile})) {
+        !rtc_prepare(*p->rtc, {p->tile}, p->g)) {
         logf("%s; using the table-driven generic kernel", stencil_last_error());
         p->base_args.rtc = nullptr;
     }
@@ -889,7 +889,7 @@ stencil_status stencil_prepare(const stencil_desc *d) {
     TuneRequest rq{STENCIL_SATURATED, d->tile_x, d->tile_y, d->zblock, d->tile_map};
     std::vector<Tile> tiles;
     for (const Cand &c : tune_candidates(&generic_ops, STENCIL_GENERIC, g, rq)) tiles.push_back(c.tile);
-    const bool ok = rtc_prepare(*tmp.rtc, tiles);
+    const bool ok = rtc_prepare(*tmp.rtc, tiles, tmp.g);
     (void)hipFree(tmp.d_tab);
     delete tmp.rtc;
     return ok ? STENCIL_OK : STENCIL_E_DEVICE;

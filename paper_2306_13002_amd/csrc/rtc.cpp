@@ -22,6 +22,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <thread>
 #include <vector>
@@ -71,6 +72,7 @@ struct SlotEmitter {
     std::string o;
     std::map<std::string, std::string> memo;  // expression -> name
     int n_add = 0, n_fma = 0, n_cell = 0, n_name = 0;
+    std::set<std::string> sums;  // by_sums: what it holds at once
 
     SlotEmitter(const RtcSpec &sp_, int ry, int w, int ph) : sp(sp_), RY(ry), W(w), phase(ph) {}
 
@@ -164,7 +166,10 @@ struct SlotEmitter {
         std::vector<std::vector<std::vector<std::string>>> v(NQ, std::vector<std::vector<std::string>>(RY));
         for (int m = 0; m < RY; ++m)
             for (int s = 0; s < NQ; ++s)
-                for (const RtcGroup &gr : sp.slots[s]) v[s][m].push_back(sum(gr, m));
+                for (const RtcGroup &gr : sp.slots[s]) {
+                    v[s][m].push_back(sum(gr, m));
+                    sums.insert(v[s][m].back());
+                }
         for (int s = 0; s < NQ; ++s) {
             if (sp.slots[s].empty()) continue;
             guard(s);
@@ -302,7 +307,7 @@ bool wide_rows(const RtcSpec &sp, int TY) { return (TY + 2 * sp.R) * sp.row_byte
 // extents and pitches share them.
 struct SpecEntry {
     std::vector<EmitPlan> emit;
-    std::map<std::vector<int>, hipFunction_t> fn;  // tx, ty, device, wide_rows
+    std::map<std::vector<int>, hipFunction_t> fn;  // tx, ty, rows per thread, device, wide_rows
 };
 std::map<std::string, SpecEntry> g_specs;  // guarded by g_mu
 
@@ -367,7 +372,9 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
     EmitPlan p;
     p.ry = ry;
     // The shared sums win where they save at least a tenth of one FMA per tap
-    // (a symmetric box of radius 3: 100 instead of 343 instructions per point).
+    // (a symmetric box of radius 3: 100 instead of 343 instructions per point)
+    // and fit the registers (40 sums there; box r = 4 with ten coefficients has
+    // 360, in scratch 30 % slower than sums per plane).
     // One FMA per tap where that is the written order too (no coefficient
     // repeats in a plane) and for F32 storage, whose rounding of the result (at
     // 2^-24) hides the sums'.  Otherwise the order that rounds no more than the
@@ -380,7 +387,11 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
     bool single = true;
     for (const auto &sl : sp.slots)
         for (const RtcGroup &g : sl) single &= g.taps.size() == 1;
-    p.order = 10 * (er.n_add + er.n_fma) <= 9 * ry * taps ? EmitPlan::SUMS
+    const bool shared = 10 * (er.n_add + er.n_fma) <= 9 * ry * taps && er.sums.size() <= 128;
+    // (Decided at four rows per thread for every tile, so that all of a
+    // stencil's kernels round alike.)
+    p.order = ry != 4                                     ? emit_plan(sp, 4).order
+              : shared                                    ? EmitPlan::SUMS
               : single || sp.eb == 4                      ? EmitPlan::TAPS
               : err.planes <= err.groups                  ? EmitPlan::PLANES
               : err.centres <= err.groups                 ? EmitPlan::CENTRES
@@ -444,12 +455,30 @@ Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
             }
         }
     }
+    sp.fitted = best;
     return best;
 }
 
-std::string rtc_generic_source(RtcSpec &sp, int TX, int TY) {
+// Rows per thread of a tile that a caller or a tuner asks for: the tile's own,
+// unless these leave few waves per SIMD (less than one, or 1.75 in long
+// z-blocks).  The chip then waits for each wave's chain, which one row per
+// thread makes shortest.  us per sweep, own rows and one: box r = 2
+// 140 x 184 x 20 at 32x8x16 36.4 and 17.8, star r = 4 20 x 30 x 110 at 32x8x64
+// 48.7 and 27.3, box r = 2 18 x 163 x 97 at 128x2x32 (one wave) 65 and 39;
+// beyond, box r = 2 167 x 181 x 213 at 32x4x32 (two waves) 62.9 and 71.7, box
+// r = 3 42 x 99 x 229 at 32x8x4 (1.5) 40 and 57.  Of 150 stencils, grids and
+// tiles the rule loses 12 % once and 3 % at most otherwise.  (The default tile
+// is fitted with its own rows.)
+GenRows rtc_rows(const RtcSpec &sp, Tile t, const Geom &g) {
+    const GenRows own = gen_rows(t.tx, t.ty);
+    if (t.tx == sp.fitted.tx && t.ty == sp.fitted.ty && t.tz == sp.fitted.tz) return own;
+    const long long per_cu = cdiv(cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, t.tz), 256);
+    const bool few = per_cu * t.tx * own.by < (std::min(t.tz, g.nz) < 16 ? 256 : 448);  // threads per CU
+    return few && t.tx * t.ty <= 256 ? GenRows{t.ty, 1} : own;
+}
+
+std::string rtc_generic_source(RtcSpec &sp, int TX, int TY, GenRows gr) {
     const int R = sp.R, W = TX + 2 * R;
-    const GenRows gr = gen_rows(TX, TY);
     const EmitPlan ep = emit_plan(sp, gr.ry);
     std::string o;
     char buf[320];
@@ -569,65 +598,69 @@ hipFunction_t rtc_function(const std::string &src, const char *kernel) {
     return fn;
 }
 
-bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles) {
-    // compile the distinct tiles concurrently
-    std::vector<Tile> uniq;
+bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles, const Geom &g) {
+    struct Shape {
+        int tx, ty, ry;
+        hipFunction_t fn = nullptr;
+    };
+    auto shape = [&](const Tile &t) { return Shape{t.tx, t.ty, rtc_rows(sp, t, g).ry}; };
+    auto same = [](const Shape &a, const Shape &b) { return a.tx == b.tx && a.ty == b.ty && a.ry == b.ry; };
+    std::vector<Shape> uniq;
     for (const Tile &t : tiles) {
-        bool seen = false;
-        for (const Tile &u : uniq) seen |= (u.tx == t.tx && u.ty == t.ty);
-        for (const RtcSpec::Kernel &k : sp.kernels) seen |= (k.tx == t.tx && k.ty == t.ty);
-        if (!seen) uniq.push_back(t);
+        const Shape k = shape(t);
+        if (std::none_of(uniq.begin(), uniq.end(), [&](const Shape &u) { return same(u, k); })) uniq.push_back(k);
     }
-    std::vector<hipFunction_t> fn(uniq.size(), nullptr);
     int dev = 0;
     (void)hipGetDevice(&dev);
     const std::string &key = spec_key(sp);
-    auto at = [&](size_t i) { return std::vector<int>{uniq[i].tx, uniq[i].ty, dev, wide_rows(sp, uniq[i].ty)}; };
-    std::vector<size_t> todo;
+    auto at = [&](const Shape &k) { return std::vector<int>{k.tx, k.ty, k.ry, dev, wide_rows(sp, k.ty)}; };
+    std::vector<Shape *> todo;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         const SpecEntry &e = g_specs[key];
-        for (size_t i = 0; i < uniq.size(); ++i) {
-            auto it = e.fn.find(at(i));
-            if (it != e.fn.end()) fn[i] = it->second;
-            else todo.push_back(i);
+        for (Shape &k : uniq) {
+            auto it = e.fn.find(at(k));
+            if (it != e.fn.end()) k.fn = it->second;
+            else todo.push_back(&k);
         }
     }
-    auto compile = [&](size_t i) {
-        fn[i] = rtc_function(rtc_generic_source(sp, uniq[i].tx, uniq[i].ty), "stencil_generic_gen");
+    // compile what is not there yet, concurrently
+    auto compile = [&](Shape &k) {
+        k.fn = rtc_function(rtc_generic_source(sp, k.tx, k.ty, {k.ty / k.ry, k.ry}), "stencil_generic_gen");
     };
     std::vector<std::thread> th;
-    for (size_t k = 1; k < todo.size(); ++k)
-        th.emplace_back([&, k] {
+    for (size_t i = 1; i < todo.size(); ++i)
+        th.emplace_back([&, i] {
             (void)hipSetDevice(dev);
-            compile(todo[k]);
+            compile(*todo[i]);
         });
-    if (!todo.empty()) compile(todo[0]);
+    if (!todo.empty()) compile(*todo[0]);
     for (auto &t : th) t.join();
     bool ok = true;
     std::lock_guard<std::mutex> lk(g_mu);
-    for (size_t i = 0; i < uniq.size(); ++i) {
-        ok &= fn[i] != nullptr;
-        if (!fn[i]) continue;
-        g_specs[key].fn[at(i)] = fn[i];
-        sp.kernels.push_back({uniq[i].tx, uniq[i].ty, fn[i]});
+    for (const Shape &k : uniq) {
+        ok &= k.fn != nullptr;
+        if (k.fn) g_specs[key].fn[at(k)] = k.fn;
+    }
+    for (const Tile &t : tiles) {
+        const Shape k = shape(t);
+        auto it = std::find_if(uniq.begin(), uniq.end(), [&](const Shape &u) { return same(u, k); });
+        if (it->fn && !sp.kernel(t)) sp.kernels.push_back({t, {t.ty / k.ry, k.ry}, it->fn});
     }
     return ok;
 }
 
 hipError_t rtc_generic_launch(const RtcSpec &sp, Tile t, const SweepArgs &a, hipStream_t s) {
-    hipFunction_t fn = nullptr;
-    for (const RtcSpec::Kernel &k : sp.kernels)
-        if (k.tx == t.tx && k.ty == t.ty) fn = k.fn;
-    if (!fn) return hipErrorInvalidImage;
+    const RtcSpec::Kernel *k = sp.kernel(t);
+    if (!k) return hipErrorInvalidImage;
     const void *src = a.src;
     void *dst = a.dst;
     Geom g = a.g;
     int zb = t.tz, remap = a.remap;
     double *part = a.part;
     void *args[] = {&src, &dst, &g, &zb, &remap, &part};
-    return hipModuleLaunchKernel(fn, (unsigned)cdiv(a.g.nx, t.tx), (unsigned)cdiv(a.g.ny, t.ty),
-                                 (unsigned)cdiv(a.g.nz, t.tz), t.tx, gen_rows(t.tx, t.ty).by, 1, 0, s, args, nullptr);
+    return hipModuleLaunchKernel(k->fn, (unsigned)cdiv(a.g.nx, t.tx), (unsigned)cdiv(a.g.ny, t.ty),
+                                 (unsigned)cdiv(a.g.nz, t.tz), t.tx, k->rows.by, 1, 0, s, args, nullptr);
 }
 
 }  // namespace stn

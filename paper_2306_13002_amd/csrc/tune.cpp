@@ -322,7 +322,7 @@ stencil_status tune_exhaustive(stencil_plan_s *p, const TuneRequest &rq, TuneEnt
         std::vector<Tile> tiles;
         for (const Cand &c : cands)
             if (c.variant == V_SATURATED) tiles.push_back(c.tile);
-        if (!tiles.empty() && !rtc_prepare(*p->rtc, tiles)) {
+        if (!tiles.empty() && !rtc_prepare(*p->rtc, tiles, p->g)) {
             logf("%s; tuning the table-driven generic kernel", stencil_last_error());
             p->base_args.rtc = nullptr;
         }

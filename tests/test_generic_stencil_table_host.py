@@ -21,7 +21,7 @@ int main() {
             Geom g{};
             g.nx = 64; g.ny = 40; g.nz = 30; g.r = 1; g.py = pitch; g.pz = pitch * 42;
             const Tile t = rtc_default_tile(sp, g);
-            const bool wide = rtc_generic_source(sp, t.tx, t.ty).find("unsigned long long>") != std::string::npos;
+            const bool wide = rtc_generic_source(sp, t.tx, t.ty, gen_rows(t.tx, t.ty)).find("unsigned long long>") != std::string::npos;
             std::printf("%d %d\n", (int)rtc_stencils(), (int)wide);
         }
 }
