@@ -455,6 +455,11 @@ Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
             }
         }
     }
+    // flat and thin grids whose partials only longer blocks keep within
+    // the allocation-free run's scratch (the table-driven kernel's) take those
+    auto blocks = [&g](Tile t) { return cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, t.tz); };
+    const Tile large{64, 4, 16};
+    if (blocks(best) > kNoallocPartials && blocks(large) <= kNoallocPartials) best = large;
     sp.fitted = best;
     return best;
 }
