@@ -127,8 +127,10 @@ __device__ __forceinline__ double generic_rows_body(const T *__restrict__ src, T
         for (int m = 0; m < RY; ++m) t[me + m * W] = (L)cv[m];
 #pragma unroll
         for (int s = 0; s < HR; ++s) t[hl[s]] = (L)hv[s];
-        if (zp < zend) pl += pzb;
-        load();  // the next plane (the last one again at the end)
+        if (zp < zend) {  // the next plane
+            pl += pzb;
+            load();
+        }
         __syncthreads();
         // slot s adds to output zp - s, if that is one of this block's
         const int lo = max(zp - k1 + 1, 0), hi = min(zp - k0, 2 * R);

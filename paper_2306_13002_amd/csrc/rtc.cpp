@@ -416,6 +416,18 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
 
 }  // namespace
 
+// Grids that stream from memory: F64 of radius 1, beyond the Infinity Cache, or
+// beyond 96 MB where a cell costs at most 16 instructions.  The time is then the
+// rate of the loads and stores, which 64 x 4 tiles with one row per thread keep
+// highest (many small blocks, rows of whole lines).  us per sweep, such tiles
+// and the fitted ones: star r = 1 256 x 200 x 160 23.3 and 26.4, 321 x 190 x 257
+// 42.7 and 51, 400^3 252 and 306, 500 x 300 x 260 159 and 159; box r = 1 of 27
+// coefficients 350^3 181 and 204, but 256 x 256 x 128 27.8 and 27.5.
+bool streams(RtcSpec &sp, const Geom &g) {
+    const double mb = 2.0 * g.nx * g.ny * g.nz * sp.eb / (1 << 20);
+    return sp.eb == 8 && sp.R == 1 && g.nx >= 64 && (mb > 320 || (mb > 96 && emit_plan(sp, 4).per_plane <= 4 * 16));
+}
+
 // Default tile of a generated kernel: the tile and z-block with the lowest
 // estimate, in cycles, of
 //   [live planes * 7 FP64 + planes * (150 + 250 cells staged per thread)
@@ -427,12 +439,17 @@ EmitPlan emit_plan(RtcSpec &sp, int ry) {
 // Where the two grids exceed the L2s (8 x 4 MB), a stencil of little
 // arithmetic takes no z-block shorter than its halo: the planes that blocks
 // load again then come from memory (star r = 3 f64 288 x 92 x 148 after other
-// work: a call of one sweep 60.9 us with z-blocks of 4, 55.3 with 8).  Small z-blocks and tiles give more waves, large ones fewer
-// planes and rings that are loaded only for their neighbours.  Measured us per
-// sweep at that rule -> now: star r = 4 f64 118 x 86 x 177 22.7 -> 15.8, f32
-// 134 x 267 x 73 25.4 -> 19.6; box r = 3 symmetric f64 127 x 164 x 252 53.0 ->
-// 45.4; box r = 3 f64 65 x 101 x 177 53.9 -> 44.0.
+// work: a call of one sweep 60.9 us with z-blocks of 4, 55.3 with 8).  Small
+// z-blocks and tiles give more waves, large ones fewer planes and rings that are
+// loaded only for their neighbours.  Measured us per sweep at that rule -> now:
+// star r = 4 f64 118 x 86 x 177 22.7 -> 15.8, f32 134 x 267 x 73 25.4 -> 19.6;
+// box r = 3 symmetric f64 127 x 164 x 252 53.0 -> 45.4; box r = 3 f64
+// 65 x 101 x 177 53.9 -> 44.0.
 Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
+    const double mb = 2.0 * g.nx * g.ny * g.nz * sp.eb / (1 << 20);
+    const Tile large{64, 4, 16};
+    auto blocks = [&g](Tile t) { return cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, t.tz); };
+    if (streams(sp, g)) return mb > 320 || blocks({64, 4, 8}) > kNoallocPartials ? large : Tile{64, 4, 8};
     static const Tile tiles[] = {{64, 16, 0}, {32, 32, 0}, {32, 16, 0}, {32, 8, 0}, {64, 4, 0}, {32, 4, 0}};
     const bool beyond_l2 = 2.0 * g.nx * g.ny * g.nz * sp.eb > (32 << 20);
     Tile best{0, 0, 0};
@@ -455,10 +472,11 @@ Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
             }
         }
     }
-    // flat and thin grids whose partials only longer blocks keep within
-    // the allocation-free run's scratch (the table-driven kernel's) take those
-    auto blocks = [&g](Tile t) { return cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, t.tz); };
-    const Tile large{64, 4, 16};
+    // streaming stars of radius 2 take tall tiles: 400^3 328 -> 276 us a sweep,
+    // 321 x 190 x 257 58 -> 52, 288 x 250 x 250 84 -> 80
+    if (sp.eb == 8 && sp.R == 2 && mb > 200 && emit_plan(sp, 4).per_plane <= 4 * 16) best = Tile{64, 16, 8};
+    // flat and thin grids whose partials only longer blocks keep within the
+    // allocation-free run's scratch (the table-driven kernel's) take those
     if (blocks(best) > kNoallocPartials && blocks(large) <= kNoallocPartials) best = large;
     sp.fitted = best;
     return best;
@@ -473,13 +491,13 @@ Tile rtc_default_tile(RtcSpec &sp, const Geom &g) {
 // beyond, box r = 2 167 x 181 x 213 at 32x4x32 (two waves) 62.9 and 71.7, box
 // r = 3 42 x 99 x 229 at 32x8x4 (1.5) 40 and 57.  Of 150 stencils, grids and
 // tiles the rule loses 12 % once and 3 % at most otherwise.  (The default tile
-// is fitted with its own rows.)
-GenRows rtc_rows(const RtcSpec &sp, Tile t, const Geom &g) {
+// is fitted with its own rows.)  Streaming grids: one row (streams).
+GenRows rtc_rows(RtcSpec &sp, Tile t, const Geom &g) {
     const GenRows own = gen_rows(t.tx, t.ty);
     if (t.tx == sp.fitted.tx && t.ty == sp.fitted.ty && t.tz == sp.fitted.tz) return own;
     const long long per_cu = cdiv(cdiv(g.nx, t.tx) * cdiv(g.ny, t.ty) * cdiv(g.nz, t.tz), 256);
     const bool few = per_cu * t.tx * own.by < (std::min(t.tz, g.nz) < 16 ? 256 : 448);  // threads per CU
-    return few && t.tx * t.ty <= 256 ? GenRows{t.ty, 1} : own;
+    return t.tx * t.ty <= 256 && (few || streams(sp, g)) ? GenRows{t.ty, 1} : own;
 }
 
 std::string rtc_generic_source(RtcSpec &sp, int TX, int TY, GenRows gr) {
@@ -608,12 +626,14 @@ bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles, const Geom &g) {
         int tx, ty, ry;
         hipFunction_t fn = nullptr;
     };
-    auto shape = [&](const Tile &t) { return Shape{t.tx, t.ty, rtc_rows(sp, t, g).ry}; };
-    auto same = [](const Shape &a, const Shape &b) { return a.tx == b.tx && a.ty == b.ty && a.ry == b.ry; };
     std::vector<Shape> uniq;
+    std::vector<size_t> of;  // per tile, its shape's index
     for (const Tile &t : tiles) {
-        const Shape k = shape(t);
-        if (std::none_of(uniq.begin(), uniq.end(), [&](const Shape &u) { return same(u, k); })) uniq.push_back(k);
+        const int ry = rtc_rows(sp, t, g).ry;
+        size_t i = 0;
+        while (i < uniq.size() && (uniq[i].tx != t.tx || uniq[i].ty != t.ty || uniq[i].ry != ry)) ++i;
+        if (i == uniq.size()) uniq.push_back(Shape{t.tx, t.ty, ry});
+        of.push_back(i);
     }
     int dev = 0;
     (void)hipGetDevice(&dev);
@@ -647,10 +667,9 @@ bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles, const Geom &g) {
         ok &= k.fn != nullptr;
         if (k.fn) g_specs[key].fn[at(k)] = k.fn;
     }
-    for (const Tile &t : tiles) {
-        const Shape k = shape(t);
-        auto it = std::find_if(uniq.begin(), uniq.end(), [&](const Shape &u) { return same(u, k); });
-        if (it->fn && !sp.kernel(t)) sp.kernels.push_back({t, {t.ty / k.ry, k.ry}, it->fn});
+    for (size_t i = 0; i < tiles.size(); ++i) {
+        const Shape &k = uniq[of[i]];
+        if (k.fn && !sp.kernel(tiles[i])) sp.kernels.push_back({tiles[i], {k.ty / k.ry, k.ry}, k.fn});
     }
     return ok;
 }

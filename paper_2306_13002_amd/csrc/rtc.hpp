@@ -58,7 +58,7 @@ hipFunction_t rtc_function(const std::string &src, const char *kernel);
 // The tile a plan takes when its descriptor leaves it open (FIXED tuning).
 Tile rtc_default_tile(RtcSpec &sp, const Geom &g);
 // Rows per thread of a plan's launches at tile t.
-GenRows rtc_rows(const RtcSpec &sp, Tile t, const Geom &g);
+GenRows rtc_rows(RtcSpec &sp, Tile t, const Geom &g);
 std::string rtc_generic_source(RtcSpec &sp, int TX, int TY, GenRows gr);
 // Stencils the process holds emission plans and kernels of.
 size_t rtc_stencils();
