@@ -1165,19 +1165,20 @@ hipError_t h3_launch(int v, Tile t, const SweepArgs &a, hipStream_t s) {
         return hipGetLastError();
     }
     if (h3_rt_tile(v, t)) {
+        // (a three-sweep run does its remainder in its first launch, which fills)
         const int k = v == V_SAT3 ? a.sweeps : (v == V_SAT2 ? 2 : 1);
 #define GO(h, kk, ry, nw)                                                                                       \
     do {                                                                                                        \
         if (a.fill)                                                                                             \
             hipLaunchKernelGGL((heat3d7_rt<h, kk, ry, nw, true>), grid, dim3(64, nw, 1), 0, s, src, dst, a.g,   \
                                a.c[0], a.c[1], t.tz, a.remap, a.part);                                          \
-        else                                                                                                    \
+        else if constexpr (h < 3 || kk == 3)                                                                    \
             hipLaunchKernelGGL((heat3d7_rt<h, kk, ry, nw, false>), grid, dim3(64, nw, 1), 0, s, src, dst, a.g,  \
                                a.c[0], a.c[1], t.tz, a.remap, a.part);                                          \
     } while (0)
 #define X(h, ry, nw)                                                                                            \
     if (RT_IS(h, ry, nw, t)) {                                                                                  \
-        if (k < 1 || k > h) return hipErrorInvalidValue;                                                        \
+        if (k < 1 || k > h || (h == 3 && k < 3 && !a.fill)) return hipErrorInvalidValue;                         \
         if (k == 1) GO(h, 1, ry, nw);                                                                           \
         if constexpr (h >= 2) if (k == 2) GO(h, 2, ry, nw);                                                     \
         if constexpr (h >= 3) if (k == 3) GO(h, 3, ry, nw);                                                     \
@@ -1238,13 +1239,13 @@ hipError_t h3_batch_launch(int v, Tile t, const BatchProb *probs, const BatchIte
         if (fill)                                                                                                \
             hipLaunchKernelGGL((heat3d7_rt_batch<h, kk, ry, nw, true>), dim3(grid), dim3(64, nw, 1), 0, s, probs, items, \
                                n_items, parity, t.tz, part);                                                     \
-        else                                                                                                     \
+        else if constexpr (h < 3 || kk == 3)                                                                     \
             hipLaunchKernelGGL((heat3d7_rt_batch<h, kk, ry, nw, false>), dim3(grid), dim3(64, nw, 1), 0, s, probs, items, \
                                n_items, parity, t.tz, part);                                                     \
     } while (0)
 #define X(h, ry, nw)                                                                                            \
     if (RT_IS(h, ry, nw, t)) {                                                                                  \
-        if (k < 1 || k > h) return hipErrorInvalidValue;                                                        \
+        if (k < 1 || k > h || (h == 3 && k < 3 && !fill)) return hipErrorInvalidValue;                         \
         if (k == 1) GO(h, 1, ry, nw);                                                                           \
         if constexpr (h >= 2) if (k == 2) GO(h, 2, ry, nw);                                                     \
         if constexpr (h >= 3) if (k == 3) GO(h, 3, ry, nw);                                                     \

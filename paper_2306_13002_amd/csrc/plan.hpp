@@ -10,7 +10,6 @@
 
 #include <vector>
 
-// Batched plan state (see batch.cpp).
 // One launch shape: form and tile as the kernels take them, and its blocks.
 struct Launch {
     int variant = 0;
@@ -19,6 +18,7 @@ struct Launch {
     long long nblocks = 0;
 };
 
+// Batched plan state (see batch.cpp).
 struct BatchClass {
     int variant = 0;   // as reported
     stn::Tile tile{};
@@ -104,7 +104,6 @@ void init_plan_fields(stencil_plan_s *p, const stencil_desc *d, const Geom &g, i
 stencil_status choose_config(stencil_plan_s *p, const stencil_desc *d);
 stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, const void *const *coef_arrays,
                                 SweepArgs &a);
-void default_launches(stencil_plan_s *p, int requested);
 Launch run_launch(const stencil_plan_s *p, int iterations);
 hipError_t run_pre(stencil_plan_s *p, void *const *fields, const Launch &l, hipStream_t s);
 hipError_t run_sweeps(stencil_plan_s *p, void *const *fields, SweepArgs a, int iterations, const Launch &l,
