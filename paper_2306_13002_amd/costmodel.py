@@ -5,7 +5,8 @@
     python -m paper_2306_13002_amd.costmodel score --data DIR --model FILE
 
 collect: for the fixed workloads (heat2d5 256^2, poisson19 129x129x257,
-wave25 512^3, heat3d7 160^3 and 400^3) and the seeded generic corpus
+wave25 512^3, heat3d7 160^3 and 400^3, and smaller, larger and ragged grids
+of each) and the seeded generic corpus
 (stencils 0..249 on their drawn 64..512 grid edges; --cap N caps the edges),
 time every candidate the tuners consider, the multi-sweep forms included --
 median of 3 runs after a warm-up, HIP events through the library's profiling
@@ -13,8 +14,8 @@ hook, seconds per sweep -- and store its 24 features (computed by the
 library) with log(seconds per sweep).  Stencils 0..199 and the fixed
 workloads train; 200..249 are held out.
 
-train: full-batch Adam on the device through stencil_mlp_train (6000
-epochs, lr 1e-2, seeded initial weights); writes the model JSON that
+train: full-batch Adam on the device through stencil_mlp_train (10000
+epochs, lr 3e-3, seeded initial weights); writes the model JSON that
 STENCIL_TUNE_MODEL plans load.  Epochs and learning rate were chosen by
 validation inside the training set (fit on the fixed workloads and stencils
 0..149, scored on 150..199); the held-out stencils played no part.
@@ -37,13 +38,19 @@ import numpy as np
 from . import synth
 from . import stencil as S
 
-FIXED = ("heat2d5", "poisson19", "wave25", "heat3d7", "heat3d7_400")
+FIXED = ("heat2d5", "poisson19", "wave25", "heat3d7", "heat3d7_400",
+         "heat2d5@64x64", "heat2d5@1000x700", "heat2d5@3000x2000", "heat3d7@61x48x53", "heat3d7@256x256x256",
+         "poisson19@31x31x31", "poisson19@60x50x40", "poisson19@255x200x100",
+         "wave25@60x60x60", "wave25@120x120x120", "wave25@200x200x200", "wave25@320x320x320")
 
 
 def stencil_spec(name, cap=None):
     """(kind, n, plan kwargs) for a workload name ('heat2d5', 'poisson19',
-    'wave25', 'heat3d7', 'heat3d7_400' or 'g<index>'); generic grids capped
-    at `cap` per edge (None: the drawn 64..512 edges)."""
+    'wave25', 'heat3d7', 'heat3d7_400', '<kind>@<extents>' or 'g<index>');
+    generic grids capped at `cap` per edge (None: the drawn 64..512 edges)."""
+    if "@" in name:
+        kind, ext = name.split("@")
+        return kind, tuple(int(v) for v in ext.split("x")), stencil_spec(kind)[2]
     if name == "heat2d5":
         return "heat2d5", (256, 256), dict(coef=(0.6, 0.1))
     if name in ("heat3d7", "heat3d7_400"):
@@ -60,14 +67,15 @@ def stencil_spec(name, cap=None):
 
 def device_inputs(name, kind, n, kw, torch, dev):
     if kind == "heat2d5":
-        u = synth.heat2d5_input(256)
+        u = synth.heat2d5_input(n[0], ny=n[1])
         return [torch.tensor(u, device=dev), torch.empty(u.shape, dtype=torch.float64, device=dev)], None
     if kind == "poisson19":
-        p, cf = synth.poisson19_inputs()
+        p, cf = (synth.poisson19_random_inputs([e + 2 for e in reversed(n)], seed=1) if "@" in name
+                 else synth.poisson19_inputs())
         return ([torch.tensor(p, device=dev), torch.empty(p.shape, dtype=torch.float32, device=dev)],
                 [torch.tensor(c, device=dev) for c in cf])
     if kind == "wave25":
-        a, b, v = synth.wave25_inputs(512)
+        a, b, v = synth.wave25_inputs(n[0])
         return [torch.tensor(a, device=dev), torch.tensor(b, device=dev)], [torch.tensor(v, device=dev)]
     if kind == "heat3d7":
         u = synth.heat3d7_input(*n)
@@ -124,7 +132,7 @@ def load(data, names):
     return rows
 
 
-def train(data, model_path, epochs=6000, lr=1e-2, train_names=None):
+def train(data, model_path, epochs=10000, lr=3e-3, train_names=None):
     names = train_names or (list(FIXED) + [f"g{i}" for i in range(200)])
     names = [nm for nm in names if os.path.exists(os.path.join(data, f"{nm}.npz"))]
     rows = load(data, names)
@@ -156,7 +164,8 @@ def score(data, model_path, names=None):
         pick = int(np.argmin(pred))
         ratios.append(secs[pick] / secs.min())
         # reference pickers: the paper's static cost (feature 21) alone, first
-        # minimum in candidate order; and the library's untuned default shape
+        # minimum in candidate order; and one shape for every grid (64 x 4,
+        # z-block 16)
         paper.append(secs[int(np.argmin(X[:, 21]))] / secs.min())
         dflt = [i for i, c in enumerate(cands) if c[0] == "saturated" and tuple(c[1][:2]) == (64, 4)
                 and c[1][2] == 16 and c[2] == "xcd"]
@@ -171,7 +180,7 @@ def score(data, model_path, names=None):
     r = np.array(ratios)
     res = {"held_out": len(r), "geomean_pick_over_best": float(np.exp(np.mean(np.log(r)))),
            "worst": float(r.max()), "frac_within_10pct": float(np.mean(r <= 1.10)),
-           "paper_static_cost_picker": summary(paper), "untuned_default": summary(default) if default else None}
+           "paper_static_cost_picker": summary(paper), "one_shape": summary(default) if default else None}
     print(json.dumps(res), flush=True)
     return res
 
@@ -228,8 +237,8 @@ def main():
     ap.add_argument("--first", type=int, default=0)
     ap.add_argument("--last", type=int, default=249)
     ap.add_argument("--fixed", action="store_true", help="also time the fixed workloads")
-    ap.add_argument("--epochs", type=int, default=6000)
-    ap.add_argument("--lr", type=float, default=1e-2)
+    ap.add_argument("--epochs", type=int, default=10000)
+    ap.add_argument("--lr", type=float, default=3e-3)
     a = ap.parse_args()
     if a.cmd == "collect":
         names = (list(FIXED) if a.fixed else []) + [f"g{i}" for i in range(a.first, a.last + 1)]

@@ -98,9 +98,35 @@ Tile default_tile(int kind, int variant, const Geom &g) {
 
 int default_remap(int) { return 1; }
 
+// GENERIC: what the saturated kernels are generated from.  Taps are grouped by
+// (dz, coefficient id), groups ordered by dz slot then id, taps in a group by
+// address.
+void fill_rtc_spec(RtcSpec &sp, const stencil_desc *d, const Geom &g) {
+    const int n = d->n_taps, r = g.r;
+    sp.R = r;
+    sp.eb = elem_bytes(d->dtype);
+    sp.row_bytes = g.py * (long long)sp.eb;
+    sp.corners = false;
+    for (int k = 0; k < n; ++k)
+        if (d->tap_off[3 * k] != 0 && d->tap_off[3 * k + 1] != 0) sp.corners = true;
+    sp.slots.assign(2 * r + 1, {});
+    for (int s = 0; s < 2 * r + 1; ++s)
+        for (int id = 0; id < d->n_coef; ++id) {
+            std::vector<std::pair<int, int>> mem;  // (dy, dx)
+            for (int t = 0; t < n; ++t)
+                if (d->tap_off[3 * t + 2] == s - r && d->tap_cid[t] == id)
+                    mem.push_back({d->tap_off[3 * t + 1], d->tap_off[3 * t]});
+            if (mem.empty()) continue;
+            std::sort(mem.begin(), mem.end());
+            RtcGroup gr;
+            gr.coef = d->coef[id];
+            for (auto &m : mem) gr.taps.push_back({m.second, m.first});
+            sp.slots[s].push_back(gr);
+        }
+}
+
 // GENERIC: build the plain and saturated tap tables and upload them.
-// Plain keeps the caller's order.  Saturated groups taps by (dz, coefficient
-// id), groups ordered by dz slot then id, taps in a group by address.
+// Plain keeps the caller's order, saturated that of the groups.
 stencil_status build_generic_tables(stencil_plan_s *p, const stencil_desc *d) {
     const int n = d->n_taps, r = p->g.r, ns = 2 * r + 1;
     std::vector<int> slot_g(ns + 1, 0), g_t, t_xy;
@@ -114,18 +140,16 @@ stencil_status build_generic_tables(stencil_plan_s *p, const stencil_desc *d) {
         for (int v : {dx, dy, dz, d->tap_cid[t]}) h = (h ^ (unsigned)v) * 16777619u;
     }
     p->taps_hash = h;
+    RtcSpec *sp = new (std::nothrow) RtcSpec();
+    if (!sp) return fail(STENCIL_E_NOMEM, "host allocation failed");
+    p->rtc = sp;
+    fill_rtc_spec(*sp, d, p->g);
     for (int s = 0; s < ns; ++s) {
         slot_g[s] = (int)g_c.size();
-        for (int id = 0; id < d->n_coef; ++id) {
-            std::vector<std::pair<int, int>> mem;  // (dy, dx)
-            for (int t = 0; t < n; ++t)
-                if (d->tap_off[3 * t + 2] == s - r && d->tap_cid[t] == id)
-                    mem.push_back({d->tap_off[3 * t + 1], d->tap_off[3 * t]});
-            if (mem.empty()) continue;
-            std::sort(mem.begin(), mem.end());
+        for (const RtcGroup &gr : sp->slots[s]) {
             g_t.push_back((int)t_xy.size());
-            g_c.push_back(d->coef[id]);
-            for (auto &m : mem) t_xy.push_back((int)(((unsigned)m.first << 16) | ((unsigned)m.second & 0xFFFFu)));
+            g_c.push_back(gr.coef);
+            for (auto &m : gr.taps) t_xy.push_back((int)(((unsigned)m.second << 16) | ((unsigned)m.first & 0xFFFFu)));
         }
     }
     slot_g[ns] = (int)g_c.size();
@@ -160,30 +184,10 @@ stencil_status build_generic_tables(stencil_plan_s *p, const stencil_desc *d) {
     t.g_t = di + o_gt;
     t.g_c = dd + c.size();
     t.t_xy = di + o_xy;
-    t.corners = false;
-    for (int k = 0; k < n; ++k)
-        if (d->tap_off[3 * k] != 0 && d->tap_off[3 * k + 1] != 0) t.corners = true;
-    // the same grouping, for the generated saturated kernels
-    RtcSpec *sp = new (std::nothrow) RtcSpec();
-    if (!sp) return fail(STENCIL_E_NOMEM, "host allocation failed");
-    sp->R = r;
-    sp->eb = elem_bytes(d->dtype);
-    sp->corners = t.corners;
-    sp->row_bytes = p->g.py * (long long)sp->eb;
-    sp->slots.resize(ns);
-    for (int s = 0; s < ns; ++s)
-        for (int gi = slot_g[s]; gi < slot_g[s + 1]; ++gi) {
-            RtcGroup gr;
-            gr.coef = g_c[gi];
-            for (int ti = g_t[gi]; ti < g_t[gi + 1]; ++ti) {
-                const int xy = t_xy[ti];
-                gr.taps.push_back({(short)(xy & 0xFFFF), xy >> 16});
-            }
-            sp->slots[s].push_back(gr);
-        }
-    p->rtc = sp;
+    t.corners = sp->corners;
     const char *tbl = std::getenv("STENCIL_GENERIC_TABLE");
     p->base_args.rtc = (tbl && std::atoi(tbl) != 0) ? nullptr : sp;
+    p->info.rtc = sp;
     return STENCIL_OK;
 }
 

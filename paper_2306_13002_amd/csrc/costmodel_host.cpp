@@ -14,6 +14,7 @@
 #include "../../include/stencil.h"
 #include "internal.hpp"
 #include "plan.hpp"
+#include "rtc.hpp"
 #include "tune.hpp"
 
 namespace stn {
@@ -22,6 +23,7 @@ stencil_status fail(stencil_status st, const char *fmt, ...);
 void logf(const char *fmt, ...);
 stencil_status hip_fail(hipError_t e, const char *what);
 stencil_status validate_desc(const stencil_desc *d, Geom &g, int &rz);
+void fill_rtc_spec(RtcSpec &sp, const stencil_desc *d, const Geom &g);
 const KindOps *ops_for(int kind);
 int elem_bytes(int dtype);
 int mlp_param_count();
@@ -67,11 +69,13 @@ StencilInfo stencil_info(const stencil_desc *d, const Geom &g) {
 //  6-8 log2 nx, ny, nz      9 log2 points      10 form: 0 plain, 1 saturated,
 //                                                 2 saturated, two sweeps per pass,
 //                                                 3 saturated, three sweeps per pass
-// 11-13 log2 tile x, y, z  14 read-footprint ratio of a tile incl. halo
+// 11-13 log2 tile x, y, z  14 read-footprint ratio of a tile incl. halo (GENERIC
+//    saturated: times the planes loaded per plane written)
 // 15 LDS bytes per block   16 estimated VGPRs  17 estimated waves per SIMD
 // 18 algorithmic bytes per point and sweep (halved by two sweeps per pass,
 //    a third of it by three)
-// 19 flops/pt of the form (several sweeps per pass: with the recomputed rings)
+// 19 flops/pt of the form (several sweeps per pass: with the recomputed rings;
+//    GENERIC saturated: FP64 instructions of the generated kernel)
 // 20 arithmetic intensity
 // 21 the paper's static cost of the form's per-point expression (Sec. Cost
 //    Model: constants 0, inputs 1, operations 10, memory accesses 100)
@@ -83,6 +87,7 @@ void cost_features(const StencilInfo &si, const Cand &c, float out[24]) {
     const bool sat = c.variant == V_SATURATED || t2 || t3;
     const double pts = (double)si.g.nx * si.g.ny * si.g.nz;
     double bytes_pt, flops, loads, ops, inputs, lds = 0, vgpr, blocks;
+    double rows = 1.0, refetch = 1.0;  // outputs per thread, planes loaded per plane written (GENERIC)
     switch (si.kind) {
     case STENCIL_HEAT2D5:
     case STENCIL_HEAT3D7: {
@@ -123,6 +128,15 @@ void cost_features(const StencilInfo &si, const Cand &c, float out[24]) {
         inputs = si.n_coef;
         if (sat) lds = 2.0 * (ty + 2 * r) * (tx + 2 * r) * 8;
         vgpr = sat ? 40 + 4.0 * (2 * r + 1) : 32;
+        if (sat && si.rtc && gen_rows(tx, ty).by) {
+            const RtcWork w = rtc_work(*si.rtc, c.tile, si.g);
+            const int out = std::min(tz, si.g.nz);
+            rows = w.rows.ry;
+            refetch = (out + 2.0 * r) / out;
+            flops = w.fp64;
+            lds = 2.0 * (ty + 2 * r) * (tx + 2 * r) * w.lds_eb;
+            vgpr = w.registers;
+        }
     }
     }
     // two sweeps per pass (POISSON19, HEAT3D7; radius 1): the state tile carries a
@@ -150,12 +164,12 @@ void cost_features(const StencilInfo &si, const Cand &c, float out[24]) {
         vgpr = 56;
     }
     blocks = std::ceil((double)si.g.nx / tx) * std::ceil((double)si.g.ny / ty) * std::ceil((double)si.g.nz / tz);
-    const double threads = (double)tx * ty * (sat ? ((t2 || t3) ? ring1 : 1.0) : tz);
+    const double threads = (double)tx * ty / rows * (sat ? ((t2 || t3) ? ring1 : 1.0) : tz);
     const double wpb = std::ceil(threads / 64);
     double waves = std::min(8.0, std::floor(512.0 / vgpr));
     if (lds > 0) waves = std::min(waves, std::floor(160.0 * 1024 / lds) * wpb / 4);
     const int rf = t3 ? 3 * r : (t2 ? 2 * r : r);
-    const double foot = sat ? (double)(tx + 2 * rf) * (ty + 2 * rf) / ((double)tx * ty)
+    const double foot = sat ? (double)(tx + 2 * rf) * (ty + 2 * rf) / ((double)tx * ty) * refetch
                             : (double)(tx + 2 * r) * (ty + 2 * r) * (tz + 2 * r) / ((double)tx * ty * tz);
     const double ws = (si.kind == STENCIL_POISSON19 ? 14.0 * 4 : (si.kind == STENCIL_WAVE25 ? 3.0 * 8 : 2.0 * si.eb)) *
                       (si.g.nx + 2.0 * r) * (si.g.ny + 2.0 * r) * (si.g.nz + 2.0 * r);
@@ -298,7 +312,14 @@ stencil_status stencil_features(const stencil_desc *d, int32_t variant, int32_t 
         tile_y < 1 || zblock < 1 ||
         (tile_map != 1 && tile_map != 2))
         return fail(STENCIL_E_INVAL, "bad candidate");
-    cost_features(stencil_info(d, g), Cand{variant, Tile{tile_x, tile_y, zblock}, tile_map == 2}, out);
+    StencilInfo si = stencil_info(d, g);
+    RtcSpec sp;
+    if (d->kind == STENCIL_GENERIC && variant == V_SATURATED) {
+        fill_rtc_spec(sp, d, g);
+        si.rtc = &sp;
+    }
+    cost_features(si, Cand{variant, Tile{tile_x, tile_y, zblock}, tile_map == 2}, out);
+    if (si.rtc) rtc_forget(sp);
     return STENCIL_OK;
 }
 

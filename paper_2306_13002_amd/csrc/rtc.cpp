@@ -544,6 +544,26 @@ std::string rtc_generic_source(RtcSpec &sp, int TX, int TY, GenRows gr) {
     return o;
 }
 
+RtcWork rtc_work(RtcSpec &sp, Tile t, const Geom &g) {
+    RtcWork w;
+    w.rows = rtc_rows(sp, t, g);
+    const EmitPlan ep = emit_plan(sp, w.rows.ry);
+    const int ry = w.rows.ry, q = 2 * sp.R + 1, out = std::min(t.tz, g.nz);
+    // slots that are not live cost nothing where they are skipped
+    const double planes = ep.guarded && ep.order != EmitPlan::SUMS ? 1.0 : (out + 2.0 * sp.R) / out;
+    w.fp64 = (double)ep.per_plane / ry * planes;
+    w.lds_eb = ep.narrow ? 4 : 8;
+    w.registers = 40 + 2.0 * q * ry * (ep.order == EmitPlan::PLANES ? 2 : 1) + 2.0 * (ry + 2 * sp.R);
+    return w;
+}
+
+void rtc_forget(RtcSpec &sp) {
+    const std::string &key = spec_key(sp);
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_specs.find(key);
+    if (it != g_specs.end() && it->second.fn.empty()) g_specs.erase(it);
+}
+
 size_t rtc_stencils() {
     std::lock_guard<std::mutex> lk(g_mu);
     return g_specs.size();

@@ -60,8 +60,18 @@ Tile rtc_default_tile(RtcSpec &sp, const Geom &g);
 // Rows per thread of a plan's launches at tile t.
 GenRows rtc_rows(RtcSpec &sp, Tile t, const Geom &g);
 std::string rtc_generic_source(RtcSpec &sp, int TX, int TY, GenRows gr);
+// A generated kernel's work at tile t over grids g, for the cost model.
+struct RtcWork {
+    GenRows rows;
+    double fp64;       // FP64 instructions per output
+    int lds_eb;        // bytes per LDS cell
+    double registers;  // estimate: accumulators, plane sums, a column of cells
+};
+RtcWork rtc_work(RtcSpec &sp, Tile t, const Geom &g);
 // Stencils the process holds emission plans and kernels of.
 size_t rtc_stencils();
+// Drop sp's entry if no kernel was made for it.
+void rtc_forget(RtcSpec &sp);
 // Compile the generated kernels of the given tiles over grids g (concurrently)
 // and keep them in sp.kernels; false if any failed.
 bool rtc_prepare(RtcSpec &sp, const std::vector<Tile> &tiles, const Geom &g);

@@ -13,6 +13,8 @@ struct stencil_plan_s;
 
 namespace stn {
 
+struct RtcSpec;
+
 // What the descriptor leaves open: variant STENCIL_AUTO and 0-valued fields
 // are searched; other values restrict the candidates.
 struct TuneRequest {
@@ -54,6 +56,7 @@ struct StencilInfo {
     int n_coef;        // distinct coefficients (coefficient arrays for POISSON19)
     int n_groups;      // saturated tap groups (GENERIC), else distinct coefficients
     double box_frac;   // fraction of taps with two or more nonzero offsets
+    RtcSpec *rtc;      // GENERIC: what its saturated kernels are generated from
 };
 
 StencilInfo stencil_info(const stencil_desc *d, const Geom &g);
