@@ -20,7 +20,8 @@
  * the interior point (i,j,k), 0 <= i < n[0], ... sits at (i+r, j+r, k+r)
  * where r is the halo width.  pitch_y >= n[0]+2r, pitch_z >= pitch_y*(n[1]+2r);
  * 0 selects the dense pitch.  2-D kinds ignore z.  The halo holds boundary
- * values; under STENCIL_BC_DIRICHLET it is never written.
+ * values; under STENCIL_BC_DIRICHLET they never change (HEAT2D5 launches of
+ * several sweeps store them again, elsewhere fields[0]'s is not written).
  *
  * Ownership: every grid pointer is a DEVICE pointer owned by the caller; the
  * library never frees or reallocates caller memory.  Arrays in the descriptor
@@ -278,10 +279,20 @@ stencil_status stencil_residuals(stencil_plan_t p, double *host_out, int32_t cou
  * HEAT3D7 plans may launch register tiles instead (tile_x, tile_y = 62 x 14,
  * 60 x 28, 58 x 26 and others), HEAT2D5 plans several sweeps per launch,
  * and FIXED POISSON19 and WAVE25 plans a tile and z-block that suit the grid,
- * all of which give the same grids bit for bit.  A plan asked for a tile
- * launches that tile. */
+ * all of which give the same grids bit for bit (stencil_plan_launch tells
+ * which).  A plan asked for a tile launches that tile. */
 stencil_status stencil_plan_config(stencil_plan_t p, int32_t *variant, int32_t *tile_x, int32_t *tile_y,
                                    int32_t *zblock, int32_t *tile_map);
+
+/* What a run of `iterations` sweeps launches on a single plan (any output
+ * pointer may be NULL): the form, tile and z-block its kernels take, which may
+ * differ from the reported ones (see stencil_plan_config), and the sweeps of a
+ * full launch.  (Library plumbing; no paper passage.)  Marching HEAT2D5 launches are reported as PLAIN with the strip's
+ * columns, the rows per block and the sweeps per launch.  Any other shape can be
+ * asked for with a descriptor of that variant and tile.  E_UNSUPPORTED for batch
+ * plans. */
+stencil_status stencil_plan_launch(stencil_plan_t p, int32_t iterations, int32_t *variant, int32_t *tile_x,
+                                   int32_t *tile_y, int32_t *zblock, int32_t *sweeps);
 
 /* Size class and launch configuration of problem `problem` (0-based, in the
  * order given to stencil_plan_batch) of a batch plan; any output pointer may

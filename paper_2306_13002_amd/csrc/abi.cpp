@@ -820,6 +820,21 @@ stencil_status stencil_plan_config(stencil_plan_t p, int32_t *variant, int32_t *
     return STENCIL_OK;
 }
 
+stencil_status stencil_plan_launch(stencil_plan_t p, int32_t iterations, int32_t *variant, int32_t *tile_x,
+                                   int32_t *tile_y, int32_t *zblock, int32_t *sweeps) {
+    if (!p) return fail(STENCIL_E_INVAL, "plan is NULL");
+    if (p->batch) return fail(STENCIL_E_UNSUPPORTED, "a batch plan launches one shape per class");
+    if (iterations < 1) return fail(STENCIL_E_INVAL, "iterations < 1");
+    const Launch l = run_launch(p, iterations);
+    const bool march = l.variant == V_MARCH;
+    if (variant) *variant = march ? (int)STENCIL_PLAIN : l.variant;
+    if (tile_x) *tile_x = march ? 64 - 2 * l.tile.tx : l.tile.tx;
+    if (tile_y) *tile_y = l.tile.ty;
+    if (zblock) *zblock = march ? l.tile.tx : l.tile.tz;
+    if (sweeps) *sweeps = launch_sweeps(p->kind, l.variant, l.tile);
+    return STENCIL_OK;
+}
+
 stencil_status stencil_batch_problem_config(stencil_plan_t p, int32_t problem, int32_t *size_class, int32_t *variant,
                                             int32_t *tile_x, int32_t *tile_y, int32_t *zblock) {
     if (!p || !p->batch) return fail(STENCIL_E_INVAL, "not a batch plan");

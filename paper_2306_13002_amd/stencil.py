@@ -72,6 +72,7 @@ def lib():
         L.stencil_run_noalloc.argtypes = [vp, ctypes.POINTER(vp), ctypes.POINTER(vp), i32, vp, vp]
         L.stencil_residual.argtypes = [vp, dp, vp]
         L.stencil_plan_config.argtypes = [vp] + [ctypes.POINTER(i32)] * 5
+        L.stencil_plan_launch.argtypes = [vp, i32] + [ctypes.POINTER(i32)] * 5
         L.stencil_plan_graph.argtypes = [vp, ctypes.POINTER(i32)]
         L.stencil_batch_problem_config.argtypes = [vp, i32] + [ctypes.POINTER(i32)] * 5
         L.stencil_plan_use_graphs.argtypes = [vp, i32]
@@ -90,7 +91,7 @@ def lib():
         L.stencil_stream.argtypes = [i32, vp, vp, vp, vp, ctypes.c_int64, i32, i32, i32, vp]
         L.stencil_stream.restype = ctypes.c_int
         for f in (L.stencil_plan, L.stencil_run, L.stencil_run_noalloc, L.stencil_residual, L.stencil_plan_config,
-                  L.stencil_plan_graph,
+                  L.stencil_plan_launch, L.stencil_plan_graph,
                   L.stencil_plan_use_graphs, L.stencil_batch_problem_config,
                   L.stencil_profile_enable, L.stencil_profile_read, L.stencil_destroy, L.stencil_plan_batch,
                   L.stencil_residuals, L.stencil_candidates, L.stencil_features, L.stencil_mlp_train,
@@ -281,6 +282,14 @@ class Plan(_GridLayout):
                                          ctypes.byref(m)))
         return {"variant": VARIANT_NAMES[v.value], "tile": (tx.value, ty.value, zb.value),
                 "tile_map": TILE_MAP_NAMES.get(m.value, m.value)}
+
+    def launch(self, iterations: int) -> dict:
+        """What a run of `iterations` sweeps launches: form, tile and the
+        sweeps of a full launch (stencil_plan_launch)."""
+        v, tx, ty, zb, k = (ctypes.c_int32() for _ in range(5))
+        _check(lib().stencil_plan_launch(self._h, int(iterations), ctypes.byref(v), ctypes.byref(tx), ctypes.byref(ty),
+                                         ctypes.byref(zb), ctypes.byref(k)))
+        return {"variant": VARIANT_NAMES[v.value], "tile": (tx.value, ty.value, zb.value), "sweeps": k.value}
 
     def use_graphs(self, enable: bool = True):
         """Replay repeated identical runs from captured HIP graphs."""
