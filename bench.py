@@ -138,9 +138,10 @@ def setup_workload(name, variant, dev, torch, synth, Plan, plan_kw=None):
         meta = dict(workload=f"{name} Jacobi heat, interior {n}, FP64, {T} sweeps + residual", interior=list(n),
                     iterations=T, bytes_per_update=16, kernel_tag=f"{name}_{variant}", source="heat.hip",
                     storage="f64", sweeps_per_launch={"saturated_t2": 2, "saturated_t3": 3}.get(variant, 1))
-        fuse = plan.config()["tile"][2] if name == "heat2d5" else 1
-        if fuse > 1:  # plain sweeps fused per launch (the first launch of a run takes the remainder)
-            meta.update(kernel_tag="heat2d5_fused", sweeps_per_launch=fuse)
+        how = plan.launch(T)
+        if name == "heat2d5" and how["sweeps"] > 1:  # several plain sweeps per launch: fused in LDS, or marching
+            meta.update(kernel_tag="heat2d5_fused" if how["tile"] == plan.config()["tile"] else "heat2d5_march",
+                        sweeps_per_launch=how["sweeps"])
         return plan, step, reset, pts * T, T, meta
     if name == "generic":
         w = synth.generic_box_workload()
@@ -161,13 +162,19 @@ def setup_workload(name, variant, dev, torch, synth, Plan, plan_kw=None):
 
         n_taps = len(w["taps"])
         n_groups = len(set((t[2], c) for t, c in zip(w["taps"], w["cids"])))
-        # FP64 operations per point update: plain = one multiply and one add per
-        # tap (the first add absent); saturated = the taps of a group summed
-        # (n_taps - n_groups adds) and one FMA per group
+        # FP64 instructions per point update: plain = one multiply and one add
+        # per tap (the first add absent); saturated = the generated kernel's
+        # shared adds and one FMA per group (the planes it loads for its
+        # neighbours only included), as the cost model counts them; flops:
+        # an FMA counts two
         if variant == "plain":
             instr, flops = 2 * n_taps - 1, 2 * n_taps - 1
         else:
-            instr, flops = n_taps, (n_taps - n_groups) + 2 * n_groups
+            from paper_2306_13002_amd import stencil as S
+            cfg = plan.config()
+            instr = float(S.features("generic", n, (variant, cfg["tile"], cfg["tile_map"]), dtype="f64", radius=r,
+                                     coef=w["coef"], taps=w["taps"], cids=w["cids"])[19])
+            flops = instr + n_groups
         meta = dict(workload=f"generic box stencil r={r}, {n_taps} taps, {len(w['coef'])} shared coefficients "
                              f"(symmetric), FP64, interior {n}, {T} sweeps + residual", interior=list(n),
                     iterations=T, bytes_per_update=16, kernel_tag=f"generic_box3_{variant}",
@@ -263,7 +270,9 @@ def time_variant(name, variant, steps, warmup, dev, torch, synth, Plan, plan_kw=
     # Each timed step continues the iteration from the previous state: the
     # same work on the same grid (the restore copy is done once, untimed).
     r = timed(plan, step, reset, steps, warmup, torch)
-    cfg = plan.config()
+    cfg = dict(plan.config())
+    if hasattr(plan, "launch"):  # what the runs launched (the tile above is the form's, as reported)
+        cfg["launch"] = {k: list(v) if k == "tile" else v for k, v in plan.launch(T).items()}
     plan.close()
     return dict(wall=r["wall"], pts=pts, sweep_ms=r["sweep_ms"], sweeps=r["sweeps"], resid=r["resid"], meta=meta,
                 cfg=cfg, T=T, sweep_ms_median=r["sweep_ms_median"], sweep_ms_best=r["sweep_ms_best"])
@@ -863,7 +872,7 @@ def secondary_jacobi(name, a, dev, torch, synth, Plan):
         traffic = read_traffic(meta["kernel_tag"], meta["source"])
         rows[v] = {"us_per_sweep": sweep_s * 1e6, "avg_launch_us": launch_s * 1e6, "sweeps_per_launch": per_launch,
                    "tile": list(r["cfg"]["tile"]), "tile_map": r["cfg"].get("tile_map"),
-                   "updates_per_s": r["pts"] * steps / r["wall"],
+                   "launch": r["cfg"].get("launch"), "updates_per_s": r["pts"] * steps / r["wall"],
                    "frac_per_pass": alg / launch_s / 1e9 / HBM_PEAK_GBS,
                    "frac_sweep_equivalent": alg * per_launch / launch_s / 1e9 / HBM_PEAK_GBS,
                    "traffic_per_launch": traffic, "traffic_gbs": traffic / launch_s / 1e9 if traffic else None}
@@ -915,7 +924,7 @@ def secondary_batch(a, dev, torch, synth, Plan):
 
 def secondary_heat2d5(a, dev, torch, synth, Plan):
     """heat2d5 256^2, 10 sweeps + residual per step (the plain form only): one
-    launch per sweep and sweeps fused per launch (tuned), and the oracle on
+    launch per sweep and several sweeps per launch (tuned), and the oracle on
     one core and on every core at once (each thread its own grid)."""
     steps = max(50, 5 * a.steps)
     rows, meta = {}, None
@@ -923,7 +932,7 @@ def secondary_heat2d5(a, dev, torch, synth, Plan):
         r = time_variant("heat2d5", "plain", steps, 5, dev, torch, synth, Plan, plan_kw=kw)
         meta = r["meta"]
         rows[label] = {"updates_per_s": r["pts"] * steps / r["wall"], "us_per_step": r["wall"] * 1e6 / steps,
-                       "tile": list(r["cfg"]["tile"])}
+                       "tile": list(r["cfg"]["tile"]), "launch": r["cfg"].get("launch")}
     out = {"workload": meta["workload"], "forms": rows,
            "fused_over_one_launch_per_sweep": rows["fused_tuned"]["updates_per_s"] /
            rows["one_launch_per_sweep"]["updates_per_s"]}
@@ -1067,6 +1076,7 @@ def bench_workload(a, dev, torch, synth, Plan):
             "sweeps_per_launch": per_launch,
             "tile": list(main_r["cfg"]["tile"]),
             "tile_map": main_r["cfg"].get("tile_map"),
+            "launch": main_r["cfg"].get("launch"),
             "launch_shape": "autotuned (exhaustive, plan time)",
             "interior": meta["interior"],
             "iterations_per_step": meta["iterations"],
@@ -1094,7 +1104,7 @@ def bench_workload(a, dev, torch, synth, Plan):
         out["saturated_forms"] = {
             v: {"value": r["pts"] * a.steps / r["wall"], "us_per_sweep": r["sweep_ms"] * 1e3 / max(1, r["sweeps"]),
                 "sweeps_per_launch": r["meta"].get("sweeps_per_launch", 1), "tile": list(r["cfg"]["tile"]),
-                "tile_map": r["cfg"].get("tile_map")} for v, r in sat.items()}
+                "tile_map": r["cfg"].get("tile_map"), "launch": r["cfg"].get("launch")} for v, r in sat.items()}
     if not a.no_plain and variant != "plain" and a.workload not in ("heat2d5", "copy"):
         pr = time_variant(a.workload, "plain", a.steps, a.warmup, dev, torch, synth, Plan)
         pv = pr["pts"] * a.steps / pr["wall"]

@@ -365,15 +365,16 @@ struct DeviceGuard {
     }
 };
 
-// Launch shapes of a FIXED (HEAT3D7 also MODEL) plan whose descriptor leaves the tile open (the
-// plan reports its form's default shape).  Results are those of that form bit
-// for bit; the residual is the same sum taken in another order.
-//  - HEAT3D7 saturated forms run their register tiles (h3_default_tile).
+// Launch shapes of a FIXED (HEAT3D7 also MODEL) plan whose descriptor leaves
+// the tile open (the plan reports its form's default shape).  Results are those
+// of that form bit for bit; the residual is the same sum taken in another order.
+//  - HEAT3D7 saturated forms run their register tiles, or the LDS tile on narrow
+//    and flat grids (h3_default_tile).
 //  - AUTO lets the plan choose the form: runs of more than one sweep advance
 //    several per pass (HEAT3D7 three), which read and write the grid once
 //    (400^3, six sweeps: 1690 us single, 530 us by threes; 61 x 48 x 53, ten
 //    sweeps and the residual: 80 us in ten launches, 47 us in four).
-//  - AUTO HEAT2D5 runs of more than one sweep march (heat2d5_march).
+//  - AUTO HEAT2D5 runs of more than two sweeps march (heat2d5_march).
 //  - POISSON19 saturated forms size their z-blocks (p19_default_tile); AUTO
 //    runs of more than one sweep make two per pass (255^3 202 -> 128 us a
 //    sweep).
@@ -529,8 +530,6 @@ stencil_status prepare_run_args(const stencil_plan_s *p, void *const *fields, co
     return STENCIL_OK;
 }
 
-// The three parts of a run on stream s (enqueued eagerly or under capture).
-// Jacobi kinds first copy the state's halo into the scratch grid.
 // Whether a run's first launch stores the scratch grid's halo itself, so that
 // no halo copy goes before it (us per call: 61 x 48 x 53 ten sweeps 49.2 ->
 // 46.6, 160^3 fifty 354 -> 349, 400^3 six 556 -> 530).
@@ -538,6 +537,9 @@ bool first_fills(const stencil_plan_s *p, const Launch &l) {
     return p->kind == STENCIL_HEAT3D7 && p->bc == STENCIL_BC_DIRICHLET && h3_fills(l.variant, l.tile);
 }
 
+// The three parts of a run on stream s (enqueued eagerly or under capture).
+// Jacobi kinds first copy the state's halo into the scratch grid, unless their
+// first launch stores it.
 hipError_t run_pre(stencil_plan_s *p, void *const *fields, const Launch &l, hipStream_t s) {
     if (p->kind == STENCIL_WAVE25 || p->bc != STENCIL_BC_DIRICHLET) return hipSuccess;
     // fused and marching HEAT2D5 sweeps write the scratch grid's boundary ring themselves
@@ -754,8 +756,8 @@ stencil_status stencil_run_noalloc(stencil_plan_t p, void *const *fields, const 
     if (!p) return fail(STENCIL_E_INVAL, "plan is NULL");
     if (p->batch) return fail(STENCIL_E_UNSUPPORTED, "batched plans have no allocation-free run");
     if (p->kind == STENCIL_GENERIC && p->variant == V_SATURATED && p->base_args.rtc)
-        return fail(STENCIL_E_UNSUPPORTED, "generated GENERIC kernels are looked up by their source text at launch; "
-                                           "the allocation-free run takes the table-driven kernel only");
+        return fail(STENCIL_E_UNSUPPORTED, "the allocation-free run does not take generated GENERIC kernels "
+                                           "(STENCIL_GENERIC_TABLE=1 plans the table-driven one)");
     const Launch l = run_launch(p, iterations);
     if (l.nblocks > kNoallocPartials)
         return fail(STENCIL_E_UNSUPPORTED, "the plan's sweep launch has %lld blocks; the allocation-free run holds at most %lld",

@@ -17,8 +17,8 @@
 // accumulators (plane accumulation), so every input value is read from memory
 // once per block.  The next plane's loads are issued before the current
 // plane's arithmetic.  The kernels generated for one stencil (rtc.cpp) choose
-// between sums shared among the slots and one FMA per tap.  The table-driven
-// kernel here (the fallback, and the allocation-free run) sums the taps that
+// between sums shared among the slots, one sum per plane, a tree per coefficient
+// and one FMA per tap.  The table-driven kernel here (the fallback, and the allocation-free run) sums the taps that
 // share a coefficient id AND a z offset (COMM/ASSOC, ascending address) and
 // multiplies once with an FMA (FMA1).
 #include "generic_body.hpp"

@@ -14,7 +14,9 @@
 // Loads: each block owns a TX x TY column tile and streams z; the centre
 // column lives in a three-deep register queue (each value loaded once), the
 // in-plane neighbours come from an LDS tile, and the next plane's loads are
-// all issued before the current plane is computed ("bulk load").
+// all issued before the current plane is computed ("bulk load").  The register
+// tiles (heat3d7_rt), which plans of open shape launch, do the same operations
+// with rows of 64 cells in registers.
 #include <algorithm>
 #include <vector>
 
