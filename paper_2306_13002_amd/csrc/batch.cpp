@@ -281,7 +281,7 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
         const int *members = b->d_members + C.member_base;
         // register tiles store the scratch grids' halos in the first launch
         const bool fills = h3_fills(C.run.variant, C.run.tile);
-        if (!fills && (e = launch_batch_copy(false, b->d_probs, members, C.n_members, C.largest, s)) != hipSuccess)
+        if (!fills && (e = launch_batch_copy(false, b->d_probs, members, C.n_members, C.halo_work, s)) != hipSuccess)
             return abort_capture(e, "halo copies");
         // a two-sweep class starts an odd sweep count with one single sweep; a
         // three-sweep class starts with one launch of the remainder's sweeps
@@ -297,7 +297,7 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
             ++launches[c];
         }
         if ((launches[c] & 1) &&
-            (e = launch_batch_copy(true, b->d_probs, members, C.n_members, C.largest, s)) != hipSuccess)
+            (e = launch_batch_copy(true, b->d_probs, members, C.n_members, C.tail_work, s)) != hipSuccess)
             return abort_capture(e, "tail copies");
         if ((e = hipEventRecord(b->evs[1 + c], s)) != hipSuccess) return abort_capture(e, "join");
         if ((e = hipStreamWaitEvent(cap, b->evs[1 + c], 0)) != hipSuccess) return abort_capture(e, "join wait");
@@ -489,7 +489,8 @@ extern "C" stencil_status stencil_plan_batch(const stencil_desc *ds, int32_t cou
         C.n_members = (int)members.size();
         for (int i : members) {
             order.push_back(i);
-            C.largest = std::max(C.largest, (long long)geoms[i].nx * geoms[i].ny * geoms[i].nz);
+            C.halo_work = std::max(C.halo_work, batch_copy_work(false, geoms[i]));
+            C.tail_work = std::max(C.tail_work, batch_copy_work(true, geoms[i]));
         }
         C.item_base = (int)items.size();
         std::vector<std::pair<int, int>> ranges;

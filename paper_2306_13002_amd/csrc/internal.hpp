@@ -112,9 +112,11 @@ hipError_t launch_periodic_fill(void *buf, int elem_bytes, const Geom &g, int rz
 hipError_t launch_fill(void *buf, long long n, int elem_bytes, double value, hipStream_t s);
 hipError_t launch_interior_copy(const void *src, void *dst, int elem_bytes, const Geom &g, int rz, hipStream_t s);
 // The halo copies (f[0] -> f[1]) or the interior copies back (tail: f[1] ->
-// f[0]) of n problems of a batch, members: their indices (device).
-hipError_t launch_batch_copy(bool tail, const BatchProb *probs, const int *members, int n, long long largest,
+// f[0]) of n problems of a batch, members: their indices (device).  work: the
+// largest batch_copy_work of them.
+hipError_t launch_batch_copy(bool tail, const BatchProb *probs, const int *members, int n, long long work,
                              hipStream_t s);
+long long batch_copy_work(bool tail, const Geom &g);
 // Two fixed-order passes: up to kReduceBlocks blocks each sum a contiguous
 // chunk of part[] into scratch[], then one block sums scratch[].
 constexpr int kReduceBlocks = 256;
@@ -134,13 +136,19 @@ hipError_t launch_stream(int op, const double *a, const double *b, const double 
 
 inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
-// Blocks per problem of a batch's copy launches (launch_batch_copy): about
-// eight elements per thread of the largest grid, at most 1024, and few enough
-// that n problems make at most 2^23 blocks (a launch holds fewer than 2^32
-// threads; the blocks stride over what is left).
-inline int batch_copy_chunks(bool tail, long long n, long long largest) {
-    const long long want = cdiv(tail ? largest : largest / 8, 2048), most = (1LL << 23) / n;
-    return (int)std::max(1LL, std::min({want, most, 1024LL}));
+// Blocks per problem of a batch's copy launches (launch_batch_copy) whose
+// largest problem has `work` pieces of one thread each.  One piece per thread
+// while that makes at most kCopyBlocks blocks, for each piece costs a load's
+// latency (one 13x10x63 grid, two sweeps: 18.6 us, 38 with one block per 16384
+// cells); then four, or eight for more than 64 problems (400^3, one sweep: 793
+// us, 801 with eight, 827 with 1024 blocks; 1001 grids of which one is 64^3
+// and all others 8^3: 103 with eight, 128 with four); and few enough that n
+// problems make at most 2^23 blocks (a launch holds fewer than 2^32 threads; the
+// blocks stride over what is left).
+constexpr long long kCopyBlocks = 1024;
+inline int batch_copy_chunks(long long n, long long work) {
+    const long long want = std::max(cdiv(work, n <= 64 ? 1024 : 2048), std::min(cdiv(work, 256), kCopyBlocks / n));
+    return (int)std::max(1LL, std::min({want, (1LL << 23) / n, 65536LL}));
 }
 
 // Largest plane (pitch_z * element size, bytes) that a kernel addressing a

@@ -25,7 +25,7 @@ struct BatchClass {
     Launch run;        // what its launches are
     int n_items = 0, item_base = 0, grid = 0;
     int n_members = 0, member_base = 0;  // its problems in BatchState::d_members
-    long long largest = 0;               // interior cells of the largest of them
+    long long halo_work = 0, tail_work = 0;  // the largest batch_copy_work of them
 };
 struct BatchState {
     int count = 0, n_items = 0;

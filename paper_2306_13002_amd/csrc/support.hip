@@ -264,12 +264,19 @@ hipError_t launch_interior_copy(const void *src, void *dst, int eb, const Geom &
     return hipGetLastError();
 }
 
-// Copies of n grids of a batch, the largest of `largest` interior cells.
-hipError_t launch_batch_copy(bool tail, const BatchProb *probs, const int *members, int n, long long largest,
+// Threads of a batch problem's copy at one piece each: the tail's cells; the
+// halo's rows, a wave each, or its side cells, which the same threads copy.
+long long batch_copy_work(bool tail, const Geom &g) {
+    if (tail) return (long long)g.nx * g.ny * g.nz;
+    const long long rows = 2LL * (g.ny + 2) + 2LL * g.nz, side = ((long long)g.nz * g.ny) << side_shift(1);
+    return std::max(rows * row_pieces(g) * 64, side);
+}
+
+hipError_t launch_batch_copy(bool tail, const BatchProb *probs, const int *members, int n, long long work,
                              hipStream_t s) {
-    const int chunks = batch_copy_chunks(tail, n, largest);
+    const int chunks = batch_copy_chunks(n, work);
     const dim3 grid((unsigned)n * (unsigned)chunks);
-    const bool w = largest < kIndex32;
+    const bool w = work < kIndex32;
     if (tail) {
         if (w) hipLaunchKernelGGL(batch_tail_kernel<unsigned>, grid, dim3(256), 0, s, probs, members, chunks);
         else hipLaunchKernelGGL(batch_tail_kernel<unsigned long long>, grid, dim3(256), 0, s, probs, members, chunks);
