@@ -6,8 +6,8 @@
 // defaults) and a work list of (problem, tile) items.  A run is one hipGraph
 // of parallel branches, one per class: a chain of work-list launches, with one
 // launch for the class's halo copies before them (before the fork if they are
-// small) and, after an odd number of them, one for the copies back after the
-// join.  The graph is captured at the first run with a
+// small) and, after an odd number of them, one for the copies back (after the
+// join if they are small).  The graph is captured at the first run with a
 // given (T, field pointers) and replayed afterwards.
 #include <hip/hip_runtime.h>
 
@@ -42,10 +42,10 @@ namespace {
 constexpr int kBatchGrid = 1 << 20;
 // Work lists at least this long are dealt to the XCDs in contiguous chunks.
 constexpr int kXcdChunkItems = 2048;
-// Halo copies of at most this many blocks in all go before the graph's fork:
-// such a run is bound by the host's launch, a larger one by its kernels (see
-// capture).
-constexpr long long kEarlyCopyBlocks = 256;
+// Halo copies of at most this many blocks in all go before the graph's fork,
+// copies back of at most that many after the join: such a run is bound by the
+// host's launch, a larger one by its kernels (see capture).
+constexpr long long kEarlyCopyBlocks = 256, kLateCopyBlocks = 8192;
 
 int size_class(const Geom &g) {
     const int m = std::max(g.nx, std::max(g.ny, g.nz));
@@ -278,32 +278,41 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
     };
     const int nc = (int)b->classes.size();
     std::vector<int> launches(nc, 0);  // per class; each launch flips the problems' buffers
-    // Small halo copies come before the fork and all copies back after the join,
+    // Small halo copies come before the fork and small copies back after the join,
     // one after the other: a graph with several roots, or leaves, costs the host
     // 10 to 20 us more per launch than the copies take (three classes of one
     // grid each, 200 blocks, one plain sweep: 64 us, 99 with all copies in the
     // branches).  Grids of edges 50, 90, 120 and 160 (463 blocks): 113, with
-    // their halos in the branches, 127 before the fork.
+    // their halos in the branches, 127 before the fork.  Where none would stand
+    // there, the first (smallest) class's do, needed or not, as the one root:
+    // five classes of register tiles, two single sweeps 122 -> 97.  Large copies
+    // back (64 grids of edges 32 to 160: 119 000 blocks) overlap the other
+    // classes' sweeps in the branches: 50 sweeps 0.5 % faster.
     auto copies = [&](bool tail, const BatchClass &C, hipStream_t s) {
         return launch_batch_copy(tail, b->d_probs, b->d_members + C.member_base, C.n_members,
                                  tail ? C.tail_work : C.halo_work, s);
     };
-    long long halo_blocks = 0;
-    for (const BatchClass &C : b->classes)
+    long long halo_blocks = 0, tail_blocks = 0;
+    for (const BatchClass &C : b->classes) {
+        tail_blocks += C.n_members * (long long)batch_copy_chunks(C.n_members, C.tail_work);
         // register tiles store the scratch grids' halos in the first launch
         if (!h3_fills(C.run.variant, C.run.tile))
             halo_blocks += C.n_members * (long long)batch_copy_chunks(C.n_members, C.halo_work);
-    const bool early = halo_blocks <= kEarlyCopyBlocks;
-    for (const BatchClass &C : b->classes)
-        if (early && !h3_fills(C.run.variant, C.run.tile) && (e = copies(false, C, cap)) != hipSuccess)
-            return abort_capture(e, "halo copies");
+    }
+    const bool early = halo_blocks > 0 && halo_blocks <= kEarlyCopyBlocks, late = tail_blocks <= kLateCopyBlocks;
+    auto before_fork = [&](int c) {
+        const BatchClass &C = b->classes[c];
+        return early ? !h3_fills(C.run.variant, C.run.tile) : c == 0 && nc > 1;
+    };
+    for (int c = 0; c < nc; ++c)
+        if (before_fork(c) && (e = copies(false, b->classes[c], cap)) != hipSuccess) return abort_capture(e, "halo copies");
     if ((e = hipEventRecord(b->evs[0], cap)) != hipSuccess) return abort_capture(e, "fork");
     for (int c = 0; c < nc; ++c) {
         const BatchClass &C = b->classes[c];
         hipStream_t s = b->side[c];
         if ((e = hipStreamWaitEvent(s, b->evs[0], 0)) != hipSuccess) return abort_capture(e, "fork wait");
         const bool fills = h3_fills(C.run.variant, C.run.tile);
-        if (!fills && !early && (e = copies(false, C, s)) != hipSuccess) return abort_capture(e, "halo copies");
+        if (!fills && !before_fork(c) && (e = copies(false, C, s)) != hipSuccess) return abort_capture(e, "halo copies");
         // a two-sweep class starts an odd sweep count with one single sweep; a
         // three-sweep class starts with one launch of the remainder's sweeps
         const int cv = C.run.variant, per = sweeps_per_launch(cv), rem = T % per;
@@ -317,11 +326,12 @@ stencil_status capture(stencil_plan_s *p, void *const *fields, int T, hipStream_
             t += adv;
             ++launches[c];
         }
+        if (!late && (launches[c] & 1) && (e = copies(true, C, s)) != hipSuccess) return abort_capture(e, "tail copies");
         if ((e = hipEventRecord(b->evs[1 + c], s)) != hipSuccess) return abort_capture(e, "join");
         if ((e = hipStreamWaitEvent(cap, b->evs[1 + c], 0)) != hipSuccess) return abort_capture(e, "join wait");
     }
     for (int c = 0; c < nc; ++c)
-        if ((launches[c] & 1) && (e = copies(true, b->classes[c], cap)) != hipSuccess) return abort_capture(e, "tail copies");
+        if (late && (launches[c] & 1) && (e = copies(true, b->classes[c], cap)) != hipSuccess) return abort_capture(e, "tail copies");
     if ((e = hipStreamEndCapture(cap, &b->graph)) != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
     if ((e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0)) != hipSuccess)
         return hip_fail(e, "hipGraphInstantiate");

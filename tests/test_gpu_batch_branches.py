@@ -9,7 +9,7 @@ from paper_2306_13002_amd.stencil import BatchPlan, Plan
 pytestmark = pytest.mark.gpu
 
 SMALL = [(26, 4, 101), (219, 17, 11), (14, 15, 245)]     # 200 halo blocks
-LARGE = [(160, 160, 160), (120, 120, 120), (40, 40, 40)]  # more than 256
+LARGE = [(160, 160, 160), (150, 160, 140), (120, 120, 120), (40, 40, 40)]  # halos more than 256, copies back more than 8192
 MIXED = [(8, 8, 8)] * 3 + [(70, 9, 20)]
 
 
